@@ -34,7 +34,7 @@ __global__ __launch_bounds__(kThreads) void k_store(unsigned char* __restrict__ 
                                                     const int* __restrict__ guard, int bits, int bs_log) {
     if (guard && ld_ctl(guard) == 0) return;
     const int lane = threadIdx.x & 63;
-    const int tile0 = blockIdx.x * kRowsPerWG + (threadIdx.x >> 6) * kTile;
+    const int tile0 = blockIdx.x * kRowsPerWG + wave_index() * kTile;
     double v[8];
     load_rows<FMT>(w, tile0, lane, n, v);
     if (divisor) {
@@ -59,7 +59,7 @@ __global__ __launch_bounds__(kThreads) void k_store(unsigned char* __restrict__ 
 // vectors they sustain 6% less.
 template <int FMT>
 __global__ __launch_bounds__(kThreads) void k_load(BasisView V, int col, double* __restrict__ x) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = wave_index();
     const int tile0 = blockIdx.x * kRowsPerWG + wave * kTile;
     Tile<FMT> t[1];
     const int cols[1] = {col};
@@ -87,7 +87,7 @@ __global__ __launch_bounds__(kThreads) void k_project(BasisView V, int j,
     if (guard && ld_ctl(guard) == 0) return;
     __shared__ double red[kThreads / 64][kMaxRestart + 1];
     __shared__ double elds[kEpiLds];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = wave_index();
     const int g = blockIdx.x;
     const int ngroups = row_groups_dev(V.np);
     const int c0 = blockIdx.y * cw;  // this workgroup's columns [c0, c1)
@@ -167,7 +167,7 @@ __global__ __launch_bounds__(kThreads) void k_subtract(BasisView V, int j, const
     const int go = load_coefficients(guard, jdev, h, j, hc);
     if (!go) return;
     __syncthreads();
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = wave_index();
     const int ngroups = row_groups_dev(V.np);
     double nrm = 0.0;
     for (int rg = blockIdx.x; rg < ngroups; rg += gridDim.x) {
@@ -222,7 +222,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_subtract_project(BasisView V, i
     __shared__ double stage[kThreads / 64][kTile];
     const int go = load_coefficients(guard, nullptr, h, j, hc);
     if (!go) return;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = wave_index();
     const int G = gridDim.x;
     const int ngroups = row_groups_dev(V.np);
     for (int i = lane; i < j; i += 64) red[wave][i] = 0.0;

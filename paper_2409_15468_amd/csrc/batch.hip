@@ -119,7 +119,7 @@ static_assert(sizeof(Shared) <= 65536, "batch solver LDS");
 // result (lane tree, then the waves in index order).
 __device__ __forceinline__ double wg_sum(double v, Shared& S) {
     v = wave_sum(v);
-    const int wave = threadIdx.x >> 6;
+    const int wave = wave_index();
     if ((threadIdx.x & 63) == 0) S.part[wave] = v;
     __syncthreads();
     double t = S.part[0];
@@ -130,12 +130,12 @@ __device__ __forceinline__ double wg_sum(double v, Shared& S) {
 }
 
 // first tile of this wave and the stride between its tiles
-__device__ __forceinline__ int tile_first() { return (threadIdx.x >> 6) * kTile; }
+__device__ __forceinline__ int tile_first() { return wave_index() * kTile; }
 constexpr int kTileStride = kBW * kTile;
 
 // ||x||^2 over the system's rows
 template <int FMT>
-__device__ double wg_sumsq(const double* x, int n, int np, Shared& S) {
+__device__ __forceinline__ double wg_sumsq(const double* x, int n, int np, Shared& S) {
     const int lane = threadIdx.x & 63;
     double t = 0.0;
     for (int tile0 = tile_first(); tile0 < np; tile0 += kTileStride) {
@@ -150,7 +150,7 @@ __device__ double wg_sumsq(const double* x, int n, int np, Shared& S) {
 // y = A x (b == NULL) or y = b - A x, one thread per row, nonzeros in CSR
 // order; returns ||y||^2.
 template <int FMT>
-__device__ double wg_spmv(const BatchItem& it, const double* x, const double* b, double* y, int np,
+__device__ __forceinline__ double wg_spmv(const BatchItem& it, const double* x, const double* b, double* y, int np,
                           Shared& S) {
     using M = Map<FMT>;
     const int lane = threadIdx.x & 63;
@@ -176,8 +176,8 @@ __device__ double wg_spmv(const BatchItem& it, const double* x, const double* b,
 
 // out[c] = <D(v_c), w> for c < jc (Fig. 1 step 5: all against the same w)
 template <int FMT>
-__device__ void wg_project(const BasisView& V, int jc, const double* w, double* out, Shared& S) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+__device__ __forceinline__ void wg_project(const BasisView& V, int jc, const double* w, double* out, Shared& S) {
+    const int lane = threadIdx.x & 63, wave = wave_index();
     for (int c = lane; c < jc; c += 64) S.red[wave][c] = 0.0;
     for (int tile0 = tile_first(); tile0 < V.np; tile0 += kTileStride) {
         double wv[8];
@@ -198,7 +198,7 @@ __device__ void wg_project(const BasisView& V, int jc, const double* w, double* 
 // w[k] += sign * sum_{c<jc} coef[c] D(v_c)[k] (the sum first, then the add);
 // returns ||w||^2 after the update.
 template <int FMT>
-__device__ double wg_update(const BasisView& V, int jc, const double* coef, double* w, int sign, Shared& S) {
+__device__ __forceinline__ double wg_update(const BasisView& V, int jc, const double* coef, double* w, int sign, Shared& S) {
     const int lane = threadIdx.x & 63;
     double t = 0.0;
     for (int tile0 = tile_first(); tile0 < V.np; tile0 += kTileStride) {
@@ -224,7 +224,7 @@ __device__ double wg_update(const BasisView& V, int jc, const double* coef, doub
 // the basis := Q(v) (step 14).  Returns true, in every thread, if a stored
 // value is not finite.
 template <int FMT>
-__device__ bool wg_store(const BasisView& V, int col, const double* w, double d, double* v) {
+__device__ __forceinline__ bool wg_store(const BasisView& V, int col, const double* w, double d, double* v) {
     const int lane = threadIdx.x & 63;
     unsigned char* vals = const_cast<unsigned char*>(V.values) + (int64_t)col * V.col_bytes;
     uint32_t* ex = V.exps ? const_cast<uint32_t*>(V.exps) + (int64_t)col * V.exp_stride : nullptr;
@@ -240,10 +240,26 @@ __device__ bool wg_store(const BasisView& V, int col, const double* w, double d,
     return __syncthreads_or(bad) != 0;
 }
 
+// The descriptor in scalar registers, its buffers in global memory.
+__device__ __forceinline__ BatchItem settled(BatchItem it) {
+    it = uniform(it);
+    it.row_ptr = global_ptr(it.row_ptr);
+    it.col = global_ptr(it.col);
+    it.val = global_ptr(it.val);
+    it.b = global_ptr(it.b);
+    it.x = global_ptr(it.x);
+    it.vals = global_ptr(it.vals);
+    it.exps = global_ptr(it.exps);
+    it.v = global_ptr(it.v);
+    it.w = global_ptr(it.w);
+    return it;
+}
+
 // One solve, all threads of the workgroup.  Scalars are computed redundantly
 // by every thread from LDS values, so every branch is uniform.
 template <int FMT>
-__device__ void batch_solve(const BatchItem& it, const BatchOpts& o, cb_result* res, Shared& S) {
+__device__ void batch_solve(const BatchItem& item, const BatchOpts& o, cb_result* res, Shared& S) {
+    const BatchItem it = settled(item);
     const int n = it.n, m = it.m, tid = threadIdx.x;
     const int np = 32 * ((n + 31) / 32);
     BasisView V;

@@ -123,6 +123,16 @@ struct BasisView {
     int32_t np;          // rows stored: n rounded up to the block size
     int32_t bits;        // FRSZ2 l (0 for float formats)
     int32_t bs_log;      // log2 of the FRSZ2 block size (5 or 6)
+
+    // A column's start, its distance formed by one 32 x 32 -> 64 bit product
+    // (col_bytes is a multiple of 256, exp_stride below 2^26): the full 64-bit
+    // product per column and load took the scalar unit three times as long.
+    __host__ __device__ const unsigned char* column(int col) const {
+        return values + (((uint64_t)(uint32_t)col * (uint32_t)(col_bytes >> 8)) << 8);
+    }
+    __host__ __device__ const uint32_t* column_exps(int col) const {
+        return exps + (uint64_t)(uint32_t)col * (uint32_t)exp_stride;
+    }
 };
 inline BasisView view_of(const cb_basis& V) {
     BasisView b;

@@ -111,18 +111,67 @@ struct Map {
     __device__ static int group_row(int t, int k) { return k * GSTRIDE + GS * t; }
 };
 
-// w (float64) at the lane's 8 rows; rows >= n read as 0.
+// The wave's index in its workgroup, in a scalar register: a tile's first row
+// is then uniform too, and every load and store below is a scalar base plus a
+// 32-bit lane offset that is the same for all columns (with a 64-bit address
+// per lane and column instead, a projection holds up to 40 registers of them).
+__device__ __forceinline__ int wave_index() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); }
+// v, the same in every lane, in scalar registers.
+template <class T>
+__device__ __forceinline__ T uniform(T v) {
+    static_assert(sizeof(T) % 4 == 0, "whole words");
+    constexpr int W = sizeof(T) / 4;
+    uint32_t raw[W];
+    __builtin_memcpy(raw, &v, sizeof(T));
+#pragma unroll
+    for (int i = 0; i < W; ++i) raw[i] = __builtin_amdgcn_readfirstlane(raw[i]);
+    __builtin_memcpy(&v, raw, sizeof(T));
+    return v;
+}
+// p as a pointer to global memory: of a pointer read from memory or LDS the
+// compiler does not know that, and flat loads take twice the address registers
+// and wait on the LDS counter too.
+template <class T>
+__device__ __forceinline__ T* global_ptr(T* p) {
+    return (T*)(__attribute__((address_space(1))) T*)(uintptr_t)p;
+}
+
+// p, uniform over the wave, held in a scalar register pair (the compiler
+// otherwise adds the lane offset to the pointer first, outside the column loop,
+// and the column's offset to that per lane)
+template <class T>
+__device__ __forceinline__ T* scalar_base(T* p) {
+    uint64_t u = uniform(reinterpret_cast<uint64_t>(p));
+    asm("" : "+s"(u));
+    return global_ptr(reinterpret_cast<T*>(u));
+}
+// An offset in bytes of a lane, as 32 bits (widened early, it would not fit the
+// loads' scalar base + 32-bit offset form).
+__device__ __forceinline__ uint32_t lane_offset(uint32_t bytes) {
+    asm("" : "+v"(bytes));
+    return bytes;
+}
+template <class T>
+__device__ __forceinline__ T* at(T* base, uint32_t lane_bytes, int more_bytes = 0) {
+    typedef __attribute__((address_space(1))) char* G;
+    return (T*)(__attribute__((address_space(1))) T*)((G)(uintptr_t)base + lane_bytes + more_bytes);
+}
+
+// w (float64) at the lane's 8 rows; rows >= n read as 0.  tile0 is uniform over
+// the wave, here and below.
 template <int FMT>
 __device__ __forceinline__ void load_rows(const double* __restrict__ w, int tile0, int lane, int n,
                                           double* wv) {
     using M = Map<FMT>;
+    const double* wt = scalar_base(w + tile0);
+    const uint32_t lo = lane_offset((uint32_t)lane * (M::GS * 8));
 #pragma unroll
     for (int k = 0; k < M::NG; ++k) {
         const int r = tile0 + M::group_row(lane, k);
         if (r + M::GS <= n) {
 #pragma unroll
             for (int p = 0; p < M::GS; p += 2) {
-                double2 t = *reinterpret_cast<const double2*>(w + r + p);
+                double2 t = *reinterpret_cast<const double2*>(at(wt, lo, (k * M::GSTRIDE + p) * 8));
                 wv[k * M::GS + p] = t.x;
                 wv[k * M::GS + p + 1] = t.y;
             }
@@ -140,17 +189,20 @@ __device__ __forceinline__ void store_rows(double* __restrict__ w, int tile0, in
                                            const double* wv) {
     using M = Map<FMT>;
     typedef double d2v __attribute__((ext_vector_type(2)));
+    double* wt = scalar_base(w + tile0);
+    const uint32_t lo = lane_offset((uint32_t)lane * (M::GS * 8));
 #pragma unroll
     for (int k = 0; k < M::NG; ++k) {
         const int r = tile0 + M::group_row(lane, k);
         if (r + M::GS <= n) {
 #pragma unroll
             for (int p = 0; p < M::GS; p += 2) {
+                double* q = at(wt, lo, (k * M::GSTRIDE + p) * 8);
                 if constexpr (NT) {
                     const d2v v = {wv[k * M::GS + p], wv[k * M::GS + p + 1]};
-                    __builtin_nontemporal_store(v, reinterpret_cast<d2v*>(w + r + p));
+                    __builtin_nontemporal_store(v, reinterpret_cast<d2v*>(q));
                 } else {
-                    *reinterpret_cast<double2*>(w + r + p) = make_double2(wv[k * M::GS + p], wv[k * M::GS + p + 1]);
+                    *reinterpret_cast<double2*>(q) = make_double2(wv[k * M::GS + p], wv[k * M::GS + p + 1]);
                 }
             }
         } else {
@@ -212,12 +264,13 @@ struct FloatTile {
     uint4 x[M::NG];
     template <int LM>
     __device__ __forceinline__ void load(const BasisView& V, int col, int tile0, int lane) {
-        const unsigned char* base = V.values + (int64_t)col * V.col_bytes;
         constexpr int esz = FMT == CB_F64 ? 8 : FMT == CB_F32 ? 4 : 2;
+        const unsigned char* base = scalar_base(V.column(col) + (int64_t)tile0 * esz);
+        const uint32_t lo = lane_offset((uint32_t)lane * 16u);
 #pragma unroll
         for (int k = 0; k < M::NG; ++k) {
             const int r = tile0 + M::group_row(lane, k);
-            x[k] = ((LM & kFull) || r < V.np) ? ld16<(LM & kStream) != 0>(base + (int64_t)r * esz)
+            x[k] = ((LM & kFull) || r < V.np) ? ld16<(LM & kStream) != 0>(at(base, lo, k * 1024))
                                               : make_uint4(0, 0, 0, 0);
         }
     }
@@ -263,14 +316,15 @@ struct Frsz2Tile32 {
     uint32_t e[2];
     template <int LM>
     __device__ __forceinline__ void load(const BasisView& V, int col, int tile0, int lane) {
-        const unsigned char* base = V.values + (int64_t)col * V.col_bytes;
-        const uint32_t* ex = V.exps + (int64_t)col * V.exp_stride;
+        const unsigned char* base = scalar_base(V.column(col) + (int64_t)tile0 * 4);
+        const uint32_t* ex = scalar_base(V.column_exps(col) + (tile0 >> LOGBS));
+        const uint32_t lo = lane_offset((uint32_t)lane * 16u), le = lane_offset((uint32_t)lane >> (LOGBS - 2) << 2);
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
             const int r = tile0 + M::group_row(lane, k);
             const bool live = (LM & kFull) || r < V.np;
-            x[k] = live ? ld16<(LM & kStream) != 0>(base + (int64_t)r * 4) : make_uint4(0, 0, 0, 0);
-            e[k] = live ? ex[r >> LOGBS] : 0u;
+            x[k] = live ? ld16<(LM & kStream) != 0>(at(base, lo, k * 1024)) : make_uint4(0, 0, 0, 0);
+            e[k] = live ? *at(ex, le, k * (1024 >> LOGBS)) : 0u;
         }
     }
     __device__ __forceinline__ double m(int q) const {
@@ -312,11 +366,12 @@ struct Frsz2Tile16 {
     uint32_t e;
     template <int LM>
     __device__ __forceinline__ void load(const BasisView& V, int col, int tile0, int lane) {
-        const unsigned char* base = V.values + (int64_t)col * V.col_bytes;
+        const unsigned char* base = scalar_base(V.column(col) + (int64_t)tile0 * 2);
+        const uint32_t* ex = scalar_base(V.column_exps(col) + (tile0 >> LOGBS));
         const int r = tile0 + M::group_row(lane, 0);
         const bool live = (LM & kFull) || r < V.np;
-        x = live ? ld16<(LM & kStream) != 0>(base + (int64_t)r * 2) : make_uint4(0, 0, 0, 0);
-        e = live ? V.exps[(int64_t)col * V.exp_stride + (r >> LOGBS)] : 0u;
+        x = live ? ld16<(LM & kStream) != 0>(at(base, lane_offset((uint32_t)lane * 16u))) : make_uint4(0, 0, 0, 0);
+        e = live ? *at(ex, lane_offset((uint32_t)lane >> (LOGBS - 3) << 2)) : 0u;
     }
     __device__ __forceinline__ double m(int q) const {
         uint32_t wd = word_of(x, q >> 1);
@@ -358,19 +413,21 @@ template <>
 struct Tile<CB_FRSZ2_21> {
     uint4 a, b;  // pieces lane and 64 + lane of the tile (b: lanes < 20)
     uint32_t e;
-    bool live;
+    int live;
     template <int LM>
     __device__ __forceinline__ void load(const BasisView& V, int col, int tile0, int lane) {
-        const unsigned char* base = V.values + (int64_t)col * V.col_bytes + (int64_t)(tile0 >> 5) * 84;
+        const unsigned char* base = scalar_base(V.column(col) + (int64_t)(tile0 >> 5) * 84);
         // bytes of whole blocks below np (a piece that straddles their end
         // stays inside the column's 256-byte-rounded storage)
         const int vbytes = (LM & kFull) ? 1344 : min(max((V.np - tile0) >> 5, 0), 16) * 84;
-        a = 16 * lane < vbytes ? ld16<(LM & kStream) != 0>(base + 16 * lane) : make_uint4(0, 0, 0, 0);
-        b = (lane < 20 && 1024 + 16 * lane < vbytes) ? ld16<(LM & kStream) != 0>(base + 1024 + 16 * lane)
+        const uint32_t lo = lane_offset((uint32_t)lane * 16u);
+        a = 16 * lane < vbytes ? ld16<(LM & kStream) != 0>(at(base, lo)) : make_uint4(0, 0, 0, 0);
+        b = (lane < 20 && 1024 + 16 * lane < vbytes) ? ld16<(LM & kStream) != 0>(at(base, lo, 1024))
                                                       : make_uint4(0, 0, 0, 0);
         const int r = tile0 + 8 * lane;
         live = (LM & kFull) || r < V.np;
-        e = live ? V.exps[(int64_t)col * V.exp_stride + (r >> 5)] : 0u;
+        const uint32_t* ex = scalar_base(V.column_exps(col) + (tile0 >> 5));
+        e = live ? *at(ex, lane_offset((uint32_t)lane >> 2 << 2)) : 0u;
     }
     __device__ __forceinline__ void codes(uint32_t* c) const {
         const int lane = threadIdx.x & 63;
@@ -440,26 +497,31 @@ struct GenTile {
     __device__ __forceinline__ void load(const BasisView& V, int col, int tile0, int lane) {
         L = V.bits;
         const int lb = V.bs_log;
-        const uint32_t* base = reinterpret_cast<const uint32_t*>(V.values + (int64_t)col * V.col_bytes);
+        // (the tile's 512 rows are whole blocks: 16 l words, tile0 / 32 l words in)
+        const uint32_t* base = scalar_base(reinterpret_cast<const uint32_t*>(V.column(col)) +
+                                           (int64_t)(tile0 >> 5) * L);
         const int r = tile0 + 8 * lane;
         const bool live = (LM & kFull) || r < V.np;
         const uint32_t start = 8u * (uint32_t)(lane & ((1 << (lb - 3)) - 1)) * (uint32_t)L;
         off = start & 31u;
         // the codes end at bit start + 8 l - 1 <= 2^lb l - 1: inside the block
         const int nw = (int)((off + 8u * (uint32_t)L + 31u) >> 5);
-        const int64_t w0 = (int64_t)(r >> lb) * (L << (lb - 5)) + (start >> 5);  // first word in the column
+        const uint32_t w0 = (((uint32_t)lane * 8u) >> lb) * (uint32_t)(L << (lb - 5)) +
+                            (start >> 5);  // first word in the tile
         // Up to three 16-byte loads from the aligned word at or below w0, when
         // the last of them ends inside the column's data (np l / 32 words);
         // otherwise (the column's last lanes) word loads.
-        const int sh = (int)(w0 & 3);
-        const int nq = (sh + nw + 3) >> 2;
-        const bool wide = WIDE && (w0 - sh) + 4 * nq <= (((int64_t)V.np * L) >> 5);
+        // (the tile starts on a 16-byte boundary: 64 l bytes per 512 rows)
+        const uint32_t sh = w0 & 3u;
+        const int nq = ((int)sh + nw + 3) >> 2;
+        const bool wide = WIDE && (int64_t)(w0 - sh) + 4 * nq <= (((int64_t)(V.np - tile0) * L) >> 5);
         if (WIDE && live && wide) {
-            const uint4* q = reinterpret_cast<const uint4*>(base + (w0 - sh));
+            const unsigned char* q = reinterpret_cast<const unsigned char*>(base);
+            const uint32_t lo = lane_offset((w0 - sh) * 4u);
             uint32_t z[12];
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
-                const uint4 a = k < nq ? ld16<(LM & kStream) != 0>(q + k) : make_uint4(0, 0, 0, 0);
+                const uint4 a = k < nq ? ld16<(LM & kStream) != 0>(at(q, lo, 16 * k)) : make_uint4(0, 0, 0, 0);
                 z[4 * k] = a.x;
                 z[4 * k + 1] = a.y;
                 z[4 * k + 2] = a.z;
@@ -475,11 +537,12 @@ struct GenTile {
 #pragma unroll
             for (int k = 0; k < 9; ++k) y[k] = z[k];
         } else {
-            const uint32_t* p = base + w0;
+            const uint32_t lo = lane_offset(w0 * 4u);
 #pragma unroll
-            for (int k = 0; k < 9; ++k) y[k] = (live && k < nw) ? ld4<(LM & kStream) != 0>(p + k) : 0u;
+            for (int k = 0; k < 9; ++k) y[k] = (live && k < nw) ? ld4<(LM & kStream) != 0>(at(base, lo, 4 * k)) : 0u;
         }
-        e = live ? V.exps[(int64_t)col * V.exp_stride + (r >> lb)] : 0u;
+        const uint32_t* ex = scalar_base(V.column_exps(col) + (tile0 >> lb));
+        e = live ? *at(ex, lane_offset(((uint32_t)lane * 8u) >> lb << 2)) : 0u;
     }
     __device__ __forceinline__ void codes(uint32_t* c) const {
         uint32_t w[9];

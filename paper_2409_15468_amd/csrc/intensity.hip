@@ -20,7 +20,7 @@ using namespace dev;
 template <int FMT>
 __global__ __launch_bounds__(kThreads) void k_intensity(BasisView V, int col, int ops, double a, double b,
                                                         double* __restrict__ partials) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = wave_index();
     const int ngroups = row_groups_dev(V.np);
     double acc = 0.0;
     for (int rg = blockIdx.x; rg < ngroups; rg += gridDim.x) {

@@ -330,7 +330,7 @@ __device__ __forceinline__ double spmv_rows_staged(int n, const int* __restrict_
                                                    double d, const double* __restrict__ b, double* __restrict__ y,
                                                    double* prod) {
     constexpr int C = kStagedMax / 64;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = wave_index();
     const int nwb = (n + 63) / 64;  // blocks of 64 rows, 4 per workgroup block
     const BlockSeq bs = xcd_blocks((nwb + 3) / 4);
     // the lane's row pointers in workgroup block gb (rows past n: no entries)
@@ -413,7 +413,7 @@ __global__ __launch_bounds__(256) void k_spmv_store(int n, int np, const int* __
     const int lane = threadIdx.x & 63;
     bool bad = false;
     for (int g = blockIdx.x; g * kRowsPerWG < np; g += gridDim.x) {
-        const int tile0 = g * kRowsPerWG + (threadIdx.x >> 6) * kTile;
+        const int tile0 = g * kRowsPerWG + wave_index() * kTile;
         double v[8];
         load_rows<FMT>(w, tile0, lane, n, v);
 #pragma unroll
