@@ -31,6 +31,7 @@
 #include "cb_internal.hpp"
 #include "epilogue.hpp"
 #include "reduce.hpp"
+#include "team.hpp"
 
 namespace cb {
 
@@ -296,6 +297,76 @@ static void enqueue_sumsq(const double* x, int n, double* part, double* dst, hip
     launch_reduce(part, G, 1, dst, 0, nullptr, s);
 }
 
+static void fill_result(cb_result* res, const State& hs, double t0) {
+    if (!res) return;
+    res->iterations = hs.iters;
+    res->restarts = hs.cycles;
+    res->reorths = hs.reorths;
+    res->breakdowns = hs.breakdowns;
+    res->converged = hs.converged;
+    res->status = hs.status;
+    res->rel_residual = hs.rel;
+    res->implicit_rel_residual = hs.gabs >= 0 ? hs.gabs / (hs.nb > 0 ? hs.nb : 1.0) : -1.0;
+    res->seconds = now_s() - t0;
+    res->basis_bytes = hs.basis_bytes;
+}
+
+// The solve by one team of resident workgroups (team.hip), which the matrix's
+// short rows, n and m allow.  Returns a cb_status, or kTeamAbandoned when the
+// team could not run (x is then still a valid start).  The exchange slots take
+// the place of w2 (or of the partial sums, for the smallest systems) and the
+// history of a launch that of H, so the workspace is that of the other path.
+static int solve_team(const cb_csr& A, const double* b, double* x, int m, int fmt, const Ws& W, const TeamArgs& opts,
+                      const double* dinv, const double* pval, double* history_host, int64_t history_cap,
+                      cb_result* res, double t0, hipStream_t s) {
+    const int n = A.n, cap = team_device_groups();
+    TeamShape sh;
+    if (spmv_lanes_per_row(n, A.nnz) != 0 || !team_shape(n, m, cap, &sh)) return kTeamAbandoned;
+    const int64_t ll_bytes = 8 * team_ll_words(sh.G, m);
+    TeamArgs a = opts;
+    if (ll_bytes <= W.L.vals - W.L.w2) a.ll = W.at<uint64_t>(W.L.w2);
+    else if (ll_bytes <= W.L.plan - W.L.part) a.ll = W.at<uint64_t>(W.L.part);
+    else return kTeamAbandoned;
+    const cb_basis V{fmt, n, m + 1, 0, W.base + W.L.vals, frsz2_bits_of(fmt) ? W.at<uint32_t>(W.L.exps) : nullptr};
+    a.rp = A.row_ptr;
+    a.ci = A.col;
+    a.val = A.val;
+    a.aval = dinv ? pval : A.val;
+    a.b = b;
+    a.x = x;
+    a.dinv = dinv;
+    a.V = view_of(V);
+    a.col_total = a.V.col_bytes + 4 * a.V.exp_stride;
+    a.w = W.at<double>(W.L.w);
+    a.st = W.at<State>(W.L.state);
+    a.hist = W.at<double>(W.L.H);
+    a.hist_cap = (m + 1) * m;
+    a.n = n;
+    a.m = m;
+    a.G = sh.G;
+    a.cs = sh.cs;
+    a.resume = 0;
+    State* hs = static_cast<State*>(g_pinned.get(sizeof(State) + (size_t)a.hist_cap * 8));
+    if (!hs) return fail(CB_ERR_HIP, "hipHostMalloc failed");
+    double* hh = reinterpret_cast<double*>(hs + 1);
+    int64_t recorded = 0;
+    TeamSeats seats(sh.G, cap);
+    for (;;) {
+        launch_team(fmt, a, s);
+        CB_HIP(hipGetLastError());
+        CB_HIP(hipMemcpyAsync(hs, a.st, sizeof(State), hipMemcpyDeviceToHost, s));
+        const bool keep = history_host && recorded < history_cap;
+        if (keep) CB_HIP(hipMemcpyAsync(hh, a.hist, (size_t)a.hist_cap * 8, hipMemcpyDeviceToHost, s));
+        CB_HIP(hipStreamSynchronize(s));
+        if (hs->status == kTeamAbandoned) return kTeamAbandoned;
+        for (int k = 0; keep && k < hs->steps && recorded < history_cap; ++k) history_host[recorded++] = hh[k] / hs->nb;
+        if (hs->stop) break;
+        a.resume = 1;
+    }
+    fill_result(res, *hs, t0);
+    return hs->status;
+}
+
 // The solve proper, on a prepared workspace.  Returns a cb_status.
 // With a Jacobi right preconditioner (dinv non-NULL) the Arnoldi SpMV runs on
 // A M^-1, whose values pval (A's values with column j scaled by dinv[j]) the
@@ -312,6 +383,17 @@ static int solve_impl(const cb_csr& A, const double* b, double* x, int m, double
     const int max_cycles = opt ? opt->max_cycles : 0;
     const int literal = opt ? opt->literal_breakdown : 0;
     const int fuse_opt = opt ? opt->fuse_updates : 0;
+
+    {
+        TeamArgs o{};
+        o.tol = tol;
+        o.eta = eta;
+        o.max_iters = max_iters;
+        o.max_cycles = max_cycles;
+        o.literal = literal;
+        const int r = solve_team(A, b, x, m, fmt, W, o, dinv, pval, history_host, history_cap, res, t0, s);
+        if (r != kTeamAbandoned) return r;
+    }
 
     State* st = W.at<State>(W.L.state);
     int32_t* flag = W.at<int32_t>(W.L.flag);
@@ -490,18 +572,7 @@ static int solve_impl(const cb_csr& A, const double* b, double* x, int m, double
         }
     }
     CB_HIP(hipStreamSynchronize(s));
-    if (res) {
-        res->iterations = hs->iters;
-        res->restarts = hs->cycles;
-        res->reorths = hs->reorths;
-        res->breakdowns = hs->breakdowns;
-        res->converged = hs->converged;
-        res->status = hs->status;
-        res->rel_residual = hs->rel;
-        res->implicit_rel_residual = hs->gabs >= 0 ? hs->gabs / (hs->nb > 0 ? hs->nb : 1.0) : -1.0;
-        res->seconds = now_s() - t0;
-        res->basis_bytes = hs->basis_bytes;
-    }
+    fill_result(res, *hs, t0);
     return hs->status;
 }
 

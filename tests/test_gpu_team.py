@@ -1,0 +1,87 @@
+"""Short-row solves run as one launch of resident workgroups: sizes around the
+edges of its tiles (512 rows), of its exchange (up to 32 workgroups read all
+partial sums, above one workgroup sums a column) and of its split of a tile
+over 8, 4, 2 and 1 waves, a row block with more entries than its staging
+buffer, and restarts so short that a solve takes several launches.
+
+The matrix has a diagonal of 4 and off-diagonals whose absolute sum is at most
+2 a row, so ||A^-1|| <= 1/2 and ||A|| <= 6 in the infinity norm; two iterates with relative residuals
+of at most 1e-10 differ by at most 2 kappa 1e-10 = 6e-10 there, and by at most
+that times sqrt(n) / 1 in the 2-norm relative to ||x|| for entries of like
+size; 1e-8 is asked for."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2409_15468_amd as cb
+import synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def near_diagonal(n, seed, wide_row=None):
+    """Rows of 4 on the diagonal with up to four neighbours at distances 1 and
+    37; row wide_row (if given) has 600 entries of 1/600."""
+    rng = np.random.default_rng(seed)
+    i = np.arange(n)
+    offs = np.array([-37, -1, 0, 1, 37])
+    cols = i[:, None] + offs
+    vals = rng.uniform(-0.5, 0.5, cols.shape)
+    vals[:, 2] = 4.0
+    keep = (cols >= 0) & (cols < n)
+    rows = np.broadcast_to(i[:, None], cols.shape)[keep]
+    c, v = cols[keep], vals[keep]
+    if wide_row is not None:
+        off = rows != wide_row
+        wide = np.unique(np.append(rng.choice(n, 600, replace=False), wide_row))
+        wv = np.full(wide.size, 1.0 / 600)
+        wv[wide == wide_row] = 4.0
+        at = np.searchsorted(rows, wide_row)
+        rows = np.concatenate([rows[:at], np.full(wide.size, wide_row), rows[at:][off[at:]]])
+        c = np.concatenate([c[:at], wide, c[at:][off[at:]]])
+        v = np.concatenate([v[:at], wv, v[at:][off[at:]]])
+    rp = np.zeros(n + 1, np.int32)
+    rp[1:] = np.cumsum(np.bincount(rows, minlength=n))
+    return synth.CSR(n, rp, c.astype(np.int32), np.ascontiguousarray(v))
+
+
+def check(A, m, fmt, seed, history_cap=1000):
+    b = A.scipy() @ np.random.default_rng(seed).uniform(-1, 1, A.n)
+    xd = torch.zeros(A.n, dtype=torch.float64, device="cuda")
+    print(f"n={A.n} m={m} {fmt}", flush=True)
+    res, hist = cb.cbgmres_solve(cb.DeviceCSR.from_host(A.row_ptr, A.col, A.val), torch.from_numpy(b).cuda(), xd, m,
+                                 1e-10, fmt, history_cap=history_cap)
+    x = xd.cpu().numpy()
+    ref = oracle.gmres(A, b, m, 1e-10, fmt, hist_cap=history_cap)
+    assert res["status"] == 0 and res["converged"]
+    assert np.linalg.norm(b - A.scipy() @ x) <= 1e-10 * (1 + 1e-6) * np.linalg.norm(b)
+    assert np.linalg.norm(x - ref.x) <= 1e-8 * np.linalg.norm(ref.x)
+    assert abs(res["iterations"] - ref.iterations) <= max(1, int(0.02 * ref.iterations))
+    assert hist.size == min(history_cap, res["iterations"])
+    k = min(5, hist.size)
+    np.testing.assert_allclose(hist[:k], ref.history[:k], rtol=1e-3)  # 64 steps of a 16-bit code at most
+    return res, x
+
+
+@pytest.mark.parametrize("n,fmt", [(1, "float64"), (31, "frsz2_32"), (511, "frsz2_16"), (512, "frsz2_21"), (513, "frsz2_32"),
+                                   (4097, "float32"), (16384, "frsz2_32"), (16385, "frsz2_32"), (16385, "frsz2_21"),
+                                   (131072, "frsz2_32"), (131073, "frsz2_16"), (131073, "float64"), (262145, "frsz2_32"),
+                                   (262145, "float64"), (524289, "frsz2_32"), (1048576, "float32"), (1048577, "frsz2_32")])
+def test_edges(n, fmt):
+    check(near_diagonal(n, n), 30, fmt, n + 1)
+
+
+@pytest.mark.parametrize("n", [700, 20000])
+def test_long_row(n):
+    check(near_diagonal(n, n, wide_row=n // 3), 30, "frsz2_32", n)
+
+
+@pytest.mark.parametrize("m", [1, 2, 3, 104, 105])
+def test_restart_lengths(m):
+    """A launch ends when the next cycle's history might not fit in m (m + 1)
+    entries: with m = 1, 2, 3 these solves take several.  104 is the longest
+    restart the team takes."""
+    res, x = check(near_diagonal(3000, m), m, "frsz2_32", m)
+    again, y = check(near_diagonal(3000, m), m, "frsz2_32", m, history_cap=0)
+    assert again["iterations"] == res["iterations"] and np.array_equal(x, y)
