@@ -430,15 +430,14 @@ int cb_intensity_run(const cb_basis* V, int32_t col, int32_t ops, double a, doub
 
 /* ======================================================================
  * Batched solves of small systems (the serving path's packing of small
- * requests into one persistent launch).  Each system is solved by the method
- * of cbgmres_solve (Fig. 1 with restarts, Eq. 4 stop test, same options and
- * statistics) inside ONE workgroup that keeps all of its state -- basis,
- * vectors, H, Givens rotations -- on the GPU for the whole solve; the
- * workgroups of a launch take systems from the list until it is empty.  A
- * system's result does not depend on the rest of the batch (fixed reduction
- * order inside the workgroup); it may differ in the last bits from
- * cbgmres_solve on the same system, whose reductions are ordered across
- * workgroups.
+ * requests into few launches).  Each system is solved by the method of
+ * cbgmres_solve (Fig. 1 with restarts, Eq. 4 stop test, same options and
+ * statistics) by a team of workgroups, one per 1024 rows, that keeps all of
+ * its state -- basis, vectors, H, Givens rotations -- on the GPU for the whole
+ * solve; a launch holds as many teams as fit the GPU.  A system's result does
+ * not depend on the rest of the batch (the team and its reduction order follow
+ * from the system's rows); it may differ in the last bits from cbgmres_solve
+ * on the same system, whose reductions are ordered otherwise.
  * ====================================================================== */
 typedef struct cb_batch_item {
     cb_csr A;                /* device CSR, 1 <= n <= cbgmres_batch_max_n() */
@@ -464,7 +463,7 @@ int32_t cbgmres_batch_max_restart(void);
 /* Device workspace bytes of one batch item; -1 if the shape is out of range. */
 int64_t cbgmres_batch_workspace_bytes(int32_t n, int32_t m, int format);
 
-/* Solve `count` systems in one launch on `stream`.  items (host array) and the
+/* Solve `count` systems on `stream`.  items (host array) and the
  * options (nullable, as for cbgmres_solve) are read before return;
  * results_host[i] receives system i's statistics (seconds = the batch's wall
  * time).  Synchronous.  Returns CB_ERR_INVALID_ARG / CB_ERR_WORKSPACE (nothing
@@ -484,9 +483,9 @@ int cbgmres_solve_batch(const cb_batch_item* items, int32_t count, const cb_opti
  * with its own HIP stream and cbgmres_solve on one request at a time).  Small
  * requests (n <= 16384, m <= cbgmres_batch_max_restart(), the paper's six
  * formats) go to a device-resident request loop: one persistent launch of
- * the one-workgroup solver whose workgroups take systems from a ring of
+ * the batched solver whose workgroups take systems from a ring of
  * descriptors while it runs, so a small request that arrives while others are
- * being solved joins that launch as soon as a workgroup is free.  Its CSR, b,
+ * being solved joins that launch as soon as enough workgroups are free.  Its CSR, b,
  * x and Krylov basis stay in device memory for the whole solve, restarts
  * included.  Arrival order is kept within each kind; small requests do not
  * wait behind large ones.  The path depends on a request's shape only and

@@ -6,17 +6,18 @@
 //  * Large requests go to solve lanes (host worker threads, each with its own
 //    HIP stream), one at a time per lane, through the multi-workgroup solver.
 //  * Small requests go to a device-resident request loop: a persistent
-//    launch of the one-workgroup solver (batch.hip, k_batch_ring) whose
-//    workgroups take systems from a ring of descriptors while it runs.  The
+//    launch of the batched solver's teams (team_ring.hip) whose workgroups
+//    take systems from a ring of descriptors while it runs.  The
 //    ring thread admits small requests by budget, places each in a device
 //    arena (its CSR, b, x and Krylov workspace stay on the GPU for the whole
 //    solve, every restart included), stages its inputs in pinned host memory
 //    and publishes its descriptor; a request that arrives while the launch
-//    runs is picked up by the next free workgroup of that same launch.  The
+//    runs is picked up by the next free workgroups of that same launch.  The
 //    ring thread collects finished systems from their done words and returns
 //    their memory to the budget.  The launch leaves when it has been idle for
-//    a while or has run for a time slice (streams sharing its hardware queue
-//    then get their turn) and is started again while work is pending.
+//    a while, has run for a time slice (streams sharing its hardware queue
+//    then get their turn) or is idle while a lane's team waits for its CUs,
+//    and is started again while work is pending.
 // Which path a request takes depends on its own shape only, and neither
 // path's arithmetic depends on what runs beside it, so a result does not
 // depend on the mix it ran in.
@@ -76,10 +77,9 @@ struct cb_server {
 
 namespace cb {
 
-// Requests up to this size go to the device-resident loop of the one-workgroup
-// solver.
-constexpr int32_t kSmallN = 16384;
-// The loop's launch: workgroups (systems solved at once), idle polls before a
+// Requests up to this size go to the device-resident loop.
+constexpr int32_t kSmallN = kRingMaxN;
+// The loop's launch: workgroups (one CU each), idle polls before a
 // workgroup leaves (~8 us apart: ~20 ms), time slice, and the host staging
 // memory for the small systems' inputs and outputs.
 constexpr int kRingGrid = 128;
@@ -448,6 +448,8 @@ static void ring_main(cb_server* S) {
             }
             if (kst != CB_OK) fail_all_small(S, kst);
         }
+        // with nothing in flight the lanes' solves get the CUs of the launch back
+        if (ring && fl.empty()) ring_idle(ring);
         if (!progressed) {
             std::unique_lock<std::mutex> lk(S->mu);
             S->cv.wait_for(lk, std::chrono::microseconds(fl.empty() ? 2000 : 100));

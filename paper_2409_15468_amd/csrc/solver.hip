@@ -1,6 +1,10 @@
 // Restarted GMRES with a compressed basis (the paper's Fig. 1) driven from
 // the host with device-resident control.
 //
+// Short-row systems of up to half a million rows are solved by one launch of
+// resident workgroups (solve_team below, team_solve.hpp); the rest of this
+// file is the launch-per-kernel path for all others.
+//
 // Every scalar decision of the method -- the re-orthogonalisation test (step
 // 7), breakdown (step 12), the Givens rotations and the implicit residual
 // (steps 16-17), the end of a cycle -- is taken on the GPU, by the last
@@ -297,7 +301,7 @@ static void enqueue_sumsq(const double* x, int n, double* part, double* dst, hip
     launch_reduce(part, G, 1, dst, 0, nullptr, s);
 }
 
-static void fill_result(cb_result* res, const State& hs, double t0) {
+void fill_result(cb_result* res, const State& hs, double seconds) {
     if (!res) return;
     res->iterations = hs.iters;
     res->restarts = hs.cycles;
@@ -307,7 +311,7 @@ static void fill_result(cb_result* res, const State& hs, double t0) {
     res->status = hs.status;
     res->rel_residual = hs.rel;
     res->implicit_rel_residual = hs.gabs >= 0 ? hs.gabs / (hs.nb > 0 ? hs.nb : 1.0) : -1.0;
-    res->seconds = now_s() - t0;
+    res->seconds = seconds;
     res->basis_bytes = hs.basis_bytes;
 }
 
@@ -351,6 +355,7 @@ static int solve_team(const cb_csr& A, const double* b, double* x, int m, int fm
     double* hh = reinterpret_cast<double*>(hs + 1);
     int64_t recorded = 0;
     TeamSeats seats(sh.G, cap);
+    seats.wait();
     for (;;) {
         launch_team(fmt, a, s);
         CB_HIP(hipGetLastError());
@@ -363,7 +368,7 @@ static int solve_team(const cb_csr& A, const double* b, double* x, int m, int fm
         if (hs->stop) break;
         a.resume = 1;
     }
-    fill_result(res, *hs, t0);
+    fill_result(res, *hs, now_s() - t0);
     return hs->status;
 }
 
@@ -572,7 +577,7 @@ static int solve_impl(const cb_csr& A, const double* b, double* x, int m, double
         }
     }
     CB_HIP(hipStreamSynchronize(s));
-    fill_result(res, *hs, t0);
+    fill_result(res, *hs, now_s() - t0);
     return hs->status;
 }
 

@@ -1,7 +1,7 @@
 """Short-row solves run as one launch of resident workgroups: sizes around the
 edges of its tiles (512 rows), of its exchange (up to 32 workgroups read all
 partial sums, above one workgroup sums a column) and of its split of a tile
-over 8, 4, 2 and 1 waves, a row block with more entries than its staging
+over 8, 4 and 2 waves, a row block with more entries than its staging
 buffer, and restarts so short that a solve takes several launches.
 
 The matrix has a diagonal of 4 and off-diagonals whose absolute sum is at most
@@ -9,6 +9,8 @@ The matrix has a diagonal of 4 and off-diagonals whose absolute sum is at most
 of at most 1e-10 differ by at most 2 kappa 1e-10 = 6e-10 there, and by at most
 that times sqrt(n) / 1 in the 2-norm relative to ||x|| for entries of like
 size; 1e-8 is asked for."""
+import time
+
 import numpy as np
 import pytest
 
@@ -85,3 +87,49 @@ def test_restart_lengths(m):
     res, x = check(near_diagonal(3000, m), m, "frsz2_32", m)
     again, y = check(near_diagonal(3000, m), m, "frsz2_32", m, history_cap=0)
     assert again["iterations"] == res["iterations"] and np.array_equal(x, y)
+
+
+def test_batch_over_several_launches():
+    """Five systems of the batch's largest size take more workgroups than the
+    GPU has CUs, so the batch runs as several launches; small ones (one and two
+    tiles, the change from 8 to 4 waves a tile) fill the gaps.  Every result is
+    that of the system alone, bit for bit, and meets its tolerance."""
+    sizes = [65536, 512, 65000, 513, 1, 65536, 1025, 64513, 65536, 3000]
+    formats = ["frsz2_32", "float64", "frsz2_21", "float32", "frsz2_16", "float16"]
+    systems, rhs = [], []
+    for i, n in enumerate(sizes):
+        A = near_diagonal(n, i)
+        b = A.scipy() @ np.random.default_rng(100 + i).uniform(-1, 1, n)
+        rhs.append((A, b))
+        systems.append((cb.DeviceCSR.from_host(A.row_ptr, A.col, A.val), torch.from_numpy(b).cuda(),
+                        torch.zeros(n, dtype=torch.float64, device="cuda"), 20, 1e-10, formats[i % 6]))
+    print("batch", flush=True)
+    res = cb.cbgmres_solve_batch(systems)
+    for i, (s, (A, b)) in enumerate(zip(systems, rhs)):
+        x = s[2].cpu().numpy()
+        assert res[i]["converged"]
+        assert np.linalg.norm(b - A.scipy() @ x) <= 1e-10 * (1 + 1e-6) * np.linalg.norm(b)
+        alone = s[:2] + (torch.zeros_like(s[2]),) + s[3:]
+        r = cb.cbgmres_solve_batch([alone])[0]
+        assert r["iterations"] == res[i]["iterations"]
+        assert np.array_equal(alone[2].cpu().numpy(), x), sizes[i]
+
+
+def test_served_small_then_large():
+    """A small request starts the serving launch (128 workgroups); the larger
+    ones after it need 138 and 256 of the GPU's CUs, so they run only if
+    that launch gives its CUs back, and the last small one only if they do."""
+    srv = cb.Server(8 << 30, 0, lanes=2)
+    for i, n in enumerate([900, 70000, 131072, 901]):
+        A = near_diagonal(n, i)
+        b = A.scipy() @ np.random.default_rng(200 + i).uniform(-1, 1, n)
+        print(f"serve n={n}", flush=True)
+        t = srv.submit(A.row_ptr, A.col, A.val, b, 20, 1e-10, "frsz2_32")
+        t0, got = time.time(), None
+        while got is None and time.time() - t0 < 20:
+            time.sleep(0.001)
+            got = srv.poll(t, n)
+        assert got is not None, "not served"
+        x = got[0]
+        assert np.linalg.norm(b - A.scipy() @ x) <= 1e-10 * (1 + 1e-6) * np.linalg.norm(b)
+    srv.close()
