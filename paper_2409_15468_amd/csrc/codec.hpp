@@ -44,11 +44,6 @@ __device__ __forceinline__ uint4 ld16(const void* p) {
         return *reinterpret_cast<const uint4*>(p);
     }
 }
-template <bool NT>
-__device__ __forceinline__ uint32_t ld4(const uint32_t* p) {
-    if constexpr (NT) return __builtin_nontemporal_load(p);
-    else return *p;
-}
 // Load mode of a tile: bit 0 the tile lies wholly inside the column (no row
 // checks), bit 1 non-temporal loads.
 constexpr int kFull = 1, kStream = 2;
@@ -479,88 +474,76 @@ struct Tile<CB_FRSZ2_21> {
     }
 };
 
-// Any l in [3, 32] (the generic formats), blocks of 32 or 64 values.  Lane t
-// owns rows 8t .. 8t+7, i.e. codes 8s .. 8s+7 (s = t mod P, P = 4 or 8 lanes
-// per block) of block t / P, which start at bit 8 s l of the block's words:
-// word 8 s l / 32, bit 8 s l % 32 of it.  The lane loads the (at most 9) words
-// that hold its 8 codes -- as words, or for wide codes as up to three aligned
-// 16-byte pieces -- and walks them with a two-word window that advances by one word whenever the bit
-// position passes 32; the window shifts use fixed register indices, so
-// nothing spills.
-template <bool WIDE>
-struct GenTile {
-    uint32_t y[9];
+// Any l in [3, 32] (the generic formats), blocks of 32 or 64 values.  A block
+// of 32 is l words with no padding, so lane t's codes 8t .. 8t+7 start at bit
+// 8 t l of the tile whatever the block size: word (t l) / 4, byte (t l) % 4 of it.  As for
+// frsz2_21 the wave loads the tile's 64 l bytes as 4 l pieces of 16 bytes (lane
+// t: pieces t and 64 + t) and hands them to the lanes through LDS when the
+// codes are used.  Shifted right by its bytes, every lane's window has code q
+// at bit l q, so the walk over the window shifts by l and has no conditions.
+// Bound by the decoding's arithmetic, not by the loads: with per-lane word
+// loads and a per-lane window (nine words, each moved under a condition after
+// each code) a projection of 2^22 x 40 took 105 us at l = 12 and 173 at l = 28,
+// now 80 and 114; frsz2_21's, whose shifts are constants, takes 87.  (Reading
+// each code's bytes from LDS at its own byte address needs no shifts, but
+// unaligned LDS reads made it 228.)
+__shared__ uint32_t xchgen[8][516];  // one tile of at most 2 KB per wave, 8 waves at most (and what a window reads past it)
+
+template <>
+struct Tile<CB_FRSZ2_GEN> {
+    uint4 a, b;  // pieces lane and 64 + lane of the tile
     uint32_t e;
-    uint32_t off;  // bit of the lane's first code in y[0]
-    int L;
+    int live, L;
     template <int LM>
     __device__ __forceinline__ void load(const BasisView& V, int col, int tile0, int lane) {
         L = V.bits;
-        const int lb = V.bs_log;
-        // (the tile's 512 rows are whole blocks: 16 l words, tile0 / 32 l words in)
-        const uint32_t* base = scalar_base(reinterpret_cast<const uint32_t*>(V.column(col)) +
-                                           (int64_t)(tile0 >> 5) * L);
-        const int r = tile0 + 8 * lane;
-        const bool live = (LM & kFull) || r < V.np;
-        const uint32_t start = 8u * (uint32_t)(lane & ((1 << (lb - 3)) - 1)) * (uint32_t)L;
-        off = start & 31u;
-        // the codes end at bit start + 8 l - 1 <= 2^lb l - 1: inside the block
-        const int nw = (int)((off + 8u * (uint32_t)L + 31u) >> 5);
-        const uint32_t w0 = (((uint32_t)lane * 8u) >> lb) * (uint32_t)(L << (lb - 5)) +
-                            (start >> 5);  // first word in the tile
-        // Up to three 16-byte loads from the aligned word at or below w0, when
-        // the last of them ends inside the column's data (np l / 32 words);
-        // otherwise (the column's last lanes) word loads.
-        // (the tile starts on a 16-byte boundary: 64 l bytes per 512 rows)
-        const uint32_t sh = w0 & 3u;
-        const int nq = ((int)sh + nw + 3) >> 2;
-        const bool wide = WIDE && (int64_t)(w0 - sh) + 4 * nq <= (((int64_t)(V.np - tile0) * L) >> 5);
-        if (WIDE && live && wide) {
-            const unsigned char* q = reinterpret_cast<const unsigned char*>(base);
-            const uint32_t lo = lane_offset((w0 - sh) * 4u);
-            uint32_t z[12];
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                const uint4 a = k < nq ? ld16<(LM & kStream) != 0>(at(q, lo, 16 * k)) : make_uint4(0, 0, 0, 0);
-                z[4 * k] = a.x;
-                z[4 * k + 1] = a.y;
-                z[4 * k + 2] = a.z;
-                z[4 * k + 3] = a.w;
-            }
-            // drop the sh words below w0: shifts by 2 and 1 with fixed indices,
-            // written as masks so that they stay register moves
-            const uint32_t m2 = (sh & 2) ? 0xFFFFFFFFu : 0u, m1 = (sh & 1) ? 0xFFFFFFFFu : 0u;
-#pragma unroll
-            for (int i = 0; i < 10; ++i) z[i] = (z[i] & ~m2) | (z[i + 2] & m2);
-#pragma unroll
-            for (int i = 0; i < 9; ++i) z[i] = (z[i] & ~m1) | (z[i + 1] & m1);
-#pragma unroll
-            for (int k = 0; k < 9; ++k) y[k] = z[k];
-        } else {
-            const uint32_t lo = lane_offset(w0 * 4u);
-#pragma unroll
-            for (int k = 0; k < 9; ++k) y[k] = (live && k < nw) ? ld4<(LM & kStream) != 0>(at(base, lo, 4 * k)) : 0u;
-        }
-        const uint32_t* ex = scalar_base(V.column_exps(col) + (tile0 >> lb));
-        e = live ? *at(ex, lane_offset(((uint32_t)lane * 8u) >> lb << 2)) : 0u;
+        const unsigned char* base = scalar_base(V.column(col) + (int64_t)(tile0 >> 5) * (4 * L));
+        // bytes of whole blocks below np (a piece that straddles their end
+        // stays inside the column's 256-byte-rounded storage)
+        const int vbytes = ((LM & kFull) ? 16 : min(max((V.np - tile0) >> 5, 0), 16)) * 4 * L;
+        const uint32_t lo = lane_offset((uint32_t)lane * 16u);
+        a = 16 * lane < vbytes ? ld16<(LM & kStream) != 0>(at(base, lo)) : make_uint4(0, 0, 0, 0);
+        b = 1024 + 16 * lane < vbytes ? ld16<(LM & kStream) != 0>(at(base, lo, 1024)) : make_uint4(0, 0, 0, 0);
+        live = (LM & kFull) || tile0 + 8 * lane < V.np;
+        const uint32_t* ex = scalar_base(V.column_exps(col) + (tile0 >> V.bs_log));
+        e = live ? *at(ex, lane_offset((uint32_t)lane >> (V.bs_log - 3) << 2)) : 0u;
     }
     __device__ __forceinline__ void codes(uint32_t* c) const {
-        uint32_t w[9];
+        const int lane = threadIdx.x & 63;
+        uint32_t* x = xchgen[threadIdx.x >> 6];
+        __builtin_amdgcn_wave_barrier();  // the slot's previous tile has been read
+        *reinterpret_cast<uint4*>(x + 4 * lane) = a;
+        if (L > 16) *reinterpret_cast<uint4*>(x + 256 + 4 * lane) = b;
+        __builtin_amdgcn_wave_barrier();
+        const uint32_t* p = x + ((lane * L) >> 2);
+        const uint32_t s = 8u * ((lane * L) & 3);
+        if (L <= 16) {
+            walk<4>(p, s, c);
+        } else if (L < 32) {
+            walk<8>(p, s, c);
+        } else {  // (no byte shift, and a shift of a word is none)
 #pragma unroll
-        for (int k = 0; k < 9; ++k) w[k] = y[k];
-        const uint32_t mask = L == 32 ? 0xFFFFFFFFu : ((1u << L) - 1u);
-        uint32_t pos = off;
+            for (int q = 0; q < 8; ++q) c[q] = live ? p[q] : 0u;
+        }
+    }
+    // c[q] = the window's bits from l q (the caller drops those past l); the 8
+    // codes lie in NW words, each code is the first word once those before it are
+    // shifted out
+    template <int NW>
+    __device__ __forceinline__ void walk(const uint32_t* p, uint32_t s, uint32_t* c) const {
+        uint32_t y[NW + 1], w[NW + 1];
+#pragma unroll
+        for (int k = 0; k <= NW; ++k) y[k] = live ? p[k] : 0u;
+#pragma unroll
+        for (int k = 0; k < NW; ++k) w[k] = __builtin_amdgcn_alignbit(y[k + 1], y[k], s);
+        w[NW] = 0u;
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
-            c[q] = __builtin_amdgcn_alignbit(w[1], w[0], pos) & mask;
-            if (q < 7) {
-                pos += (uint32_t)L;
-                const bool adv = pos >= 32u;
-                // codes q+1 .. 7 need at most words 0 .. 7-q of the window
+            c[q] = w[0];
+            const int left = (NW * (7 - q) + 7) / 8;  // words of the codes after q at most
 #pragma unroll
-                for (int k = 0; k < 8 - q; ++k) w[k] = adv ? w[k + 1] : w[k];
-                pos = adv ? pos - 32u : pos;
-            }
+            for (int k = 0; k < NW; ++k)
+                if (k < left) w[k] = __builtin_amdgcn_alignbit(w[k + 1], w[k], L);
         }
     }
     __device__ __forceinline__ double m_of(uint32_t c) const {
@@ -589,8 +572,6 @@ struct GenTile {
         for (int q = 0; q < 8; ++q) out[q] = ldexp(m_of(c[q]), se);
     }
 };
-template <> struct Tile<CB_FRSZ2_GEN> : GenTile<false> {};
-template <> struct Tile<CB_FRSZ2_GENW> : GenTile<true> {};
 
 // Load U columns of a tile (load mode M).
 template <int FMT, int U, int LM>

@@ -127,7 +127,6 @@ void launch_team(int fmt, const TeamArgs& a, hipStream_t s) {
         CB_TEAM_CASE(CB_FRSZ2_16)
         CB_TEAM_CASE(CB_FRSZ2_21)
         CB_TEAM_CASE(CB_FRSZ2_GEN)
-        CB_TEAM_CASE(CB_FRSZ2_GENW)
         CB_TEAM_CASE(CB_FRSZ2_16_B64)
         CB_TEAM_CASE(CB_FRSZ2_32_B64)
         default:

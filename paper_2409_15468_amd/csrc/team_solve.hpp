@@ -307,7 +307,7 @@ __device__ __forceinline__ void read_rows(const Ctx& x, double* wv) {
 // waves per SIMD (64 registers of tiles; more spill).
 template <int FMT>
 constexpr int kSlotsOf = FMT == CB_F64 ? 2 : FMT == CB_FRSZ2_32 || FMT == CB_FRSZ2_32_B64 || FMT == CB_FRSZ2_21 ? 6
-                     : is_generic<FMT> ? 4 : 8;
+                     : is_generic<FMT> ? 3 : 8;
 // the wave's columns among the first jc
 __device__ __forceinline__ int columns_of(const Ctx& x, int jc) { return (jc - x.p + x.cs - 1) >> x.lcs; }
 // Makes the stored words opaque where they are used again: otherwise the

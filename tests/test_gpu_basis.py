@@ -115,3 +115,29 @@ def test_project_is_deterministic():
     h1 = cb.cb_cgs_project(V, 12, w).cpu().numpy()
     h2 = cb.cb_cgs_project(V, 12, w).cpu().numpy()
     assert np.array_equal(h1.view(np.uint64), h2.view(np.uint64))
+
+
+@pytest.mark.parametrize("bits", [3, 15, 16, 17, 25, 31])
+@pytest.mark.parametrize("n", [33, 545, 1057])
+def test_generic_width_tiles(bits, n):
+    """The generic widths' tiles where their window changes (16 and 17 bits),
+    at their ends, and with a last tile of one or two blocks: project and
+    subtract against the oracle on the decoded columns, within 1e-12 of
+    sum_k |v_ik w_k| and 1e-14 of |w| + sum_i |h_i v_ik|, the bounds of the
+    other formats' projections and updates."""
+    j = 9
+    rng = np.random.default_rng(1000 * bits + n)
+    V = cb.Basis.empty(f"frsz2_{bits}", n, j)
+    dec = np.zeros((n, j), order="F")
+    for c in range(j):
+        x = rng.standard_normal(n) * 10.0 ** rng.uniform(-3, 0, n)
+        cb.cb_basis_store(V, c, torch.from_numpy(x).cuda())
+        vals, exps, _ = oracle.basis_encode(f"frsz2_{bits}", x)
+        dec[:, c] = oracle.basis_decode(f"frsz2_{bits}", vals, exps, n)
+    w = rng.standard_normal(n)
+    wd = torch.from_numpy(w).cuda()
+    h = cb.cb_cgs_project(V, j, wd).cpu().numpy()
+    assert np.all(np.abs(h - oracle.cgs_project(dec, w)) <= 1e-12 * (np.abs(dec).T @ np.abs(w)))
+    cb.cb_cgs_subtract(V, j, torch.from_numpy(h).cuda(), wd)
+    err = np.abs(wd.cpu().numpy() - oracle.cgs_subtract(dec, h, w))
+    assert np.all(err <= 1e-14 * (np.abs(w) + np.abs(dec) @ np.abs(h)))
