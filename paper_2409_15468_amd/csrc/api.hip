@@ -288,8 +288,13 @@ int cb_cgs_subtract_project(const cb_basis* V, int32_t j, const double* h, doubl
         return fail(CB_ERR_WORKSPACE, "workspace %zu < %lld bytes", work_bytes,
                     (long long)reduce_workspace_bytes(V->n, j + 1, 0));
     hipStream_t s = (hipStream_t)stream;
-    launch_zero_counter(static_cast<unsigned*>(work), s);
-    launch_subtract_project(V->format, *V, j, h, w, partials_of(work), nullptr, store_epi(out, work), s);
+    // two launches without the ticket counters, whose place the partial sums take too
+    Epi e{};
+    e.mode = EPI_PARTIALS;
+    double* part = static_cast<double*>(work);
+    const int G = launch_subtract_project(V->format, *V, j, h, w, part, reduce_workspace_bytes(V->n, j + 1, 0) / 8,
+                                          nullptr, e, s);
+    launch_reduce(part, G, j + 1, out, 0, nullptr, s);
     CB_HIP(hipGetLastError());
     return CB_OK;
 }

@@ -45,8 +45,9 @@ __device__ __forceinline__ uint4 ld16(const void* p) {
     }
 }
 // Load mode of a tile: bit 0 the tile lies wholly inside the column (no row
-// checks), bit 1 non-temporal loads.
-constexpr int kFull = 1, kStream = 2;
+// checks), bit 1 non-temporal loads, bit 2 buffer loads bounded by the column's
+// rows (a tile partly or wholly past them reads as 0 there, without conditions).
+constexpr int kFull = 1, kStream = 2, kBound = 4;
 __device__ __forceinline__ uint32_t word_of(const uint4& a, int i) {
     return i == 0 ? a.x : i == 1 ? a.y : i == 2 ? a.z : a.w;
 }
@@ -151,6 +152,22 @@ __device__ __forceinline__ T* at(T* base, uint32_t lane_bytes, int more_bytes = 
     typedef __attribute__((address_space(1))) char* G;
     return (T*)(__attribute__((address_space(1))) T*)((G)(uintptr_t)base + lane_bytes + more_bytes);
 }
+// A run of `bytes` bytes at p for loads that read 0 past its end (p and bytes
+// uniform over the wave).
+struct Run {
+    __amdgpu_buffer_rsrc_t r;
+    __device__ __forceinline__ Run(const void* p, int bytes)
+        : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00027000)) {}
+    __device__ __forceinline__ uint4 b16(uint32_t lane_bytes, int more = 0) const {
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_bytes + more, 0, 0);
+        return make_uint4(v.x, v.y, v.z, v.w);
+    }
+    __device__ __forceinline__ uint32_t b4(uint32_t lane_bytes, int more = 0) const {
+        return __builtin_amdgcn_raw_buffer_load_b32(r, (int)lane_bytes + more, 0, 0);
+    }
+};
+// rows of the tile below np
+__device__ __forceinline__ int tile_rows(int np, int tile0) { return min(max(np - tile0, 0), kTile); }
 
 // w (float64) at the lane's 8 rows; rows >= n read as 0.  tile0 is uniform over
 // the wave, here and below.
@@ -262,6 +279,12 @@ struct FloatTile {
         constexpr int esz = FMT == CB_F64 ? 8 : FMT == CB_F32 ? 4 : 2;
         const unsigned char* base = scalar_base(V.column(col) + (int64_t)tile0 * esz);
         const uint32_t lo = lane_offset((uint32_t)lane * 16u);
+        if constexpr ((LM & kBound) != 0) {
+            const Run run(base, tile_rows(V.np, tile0) * esz);
+#pragma unroll
+            for (int k = 0; k < M::NG; ++k) x[k] = run.b16(lo, k * 1024);
+            return;
+        }
 #pragma unroll
         for (int k = 0; k < M::NG; ++k) {
             const int r = tile0 + M::group_row(lane, k);
@@ -314,6 +337,16 @@ struct Frsz2Tile32 {
         const unsigned char* base = scalar_base(V.column(col) + (int64_t)tile0 * 4);
         const uint32_t* ex = scalar_base(V.column_exps(col) + (tile0 >> LOGBS));
         const uint32_t lo = lane_offset((uint32_t)lane * 16u), le = lane_offset((uint32_t)lane >> (LOGBS - 2) << 2);
+        if constexpr ((LM & kBound) != 0) {
+            const int rows = tile_rows(V.np, tile0);
+            const Run run(base, rows * 4), exps(ex, rows >> LOGBS << 2);
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                x[k] = run.b16(lo, k * 1024);
+                e[k] = exps.b4(le, k * (1024 >> LOGBS));
+            }
+            return;
+        }
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
             const int r = tile0 + M::group_row(lane, k);
@@ -363,6 +396,12 @@ struct Frsz2Tile16 {
     __device__ __forceinline__ void load(const BasisView& V, int col, int tile0, int lane) {
         const unsigned char* base = scalar_base(V.column(col) + (int64_t)tile0 * 2);
         const uint32_t* ex = scalar_base(V.column_exps(col) + (tile0 >> LOGBS));
+        if constexpr ((LM & kBound) != 0) {
+            const int rows = tile_rows(V.np, tile0);
+            x = Run(base, rows * 2).b16(lane_offset((uint32_t)lane * 16u));
+            e = Run(ex, rows >> LOGBS << 2).b4(lane_offset((uint32_t)lane >> (LOGBS - 3) << 2));
+            return;
+        }
         const int r = tile0 + M::group_row(lane, 0);
         const bool live = (LM & kFull) || r < V.np;
         x = live ? ld16<(LM & kStream) != 0>(at(base, lane_offset((uint32_t)lane * 16u))) : make_uint4(0, 0, 0, 0);
@@ -414,14 +453,24 @@ struct Tile<CB_FRSZ2_21> {
         const unsigned char* base = scalar_base(V.column(col) + (int64_t)(tile0 >> 5) * 84);
         // bytes of whole blocks below np (a piece that straddles their end
         // stays inside the column's 256-byte-rounded storage)
-        const int vbytes = (LM & kFull) ? 1344 : min(max((V.np - tile0) >> 5, 0), 16) * 84;
+        const int vbytes = (LM & kFull) ? 1344 : (tile_rows(V.np, tile0) >> 5) * 84;
         const uint32_t lo = lane_offset((uint32_t)lane * 16u);
+        const uint32_t* ex = scalar_base(V.column_exps(col) + (tile0 >> 5));
+        if constexpr ((LM & kBound) != 0) {
+            const Run run(base, (vbytes + 15) & ~15);
+            a = run.b16(lo);
+            b = run.b16(lo, 1024);
+            // (rows past the end that share a piece with the last block decode
+            // to less than 2^-1040: exponent 0)
+            live = 1;
+            e = Run(ex, vbytes / 84 * 4).b4(lane_offset((uint32_t)lane >> 2 << 2));
+            return;
+        }
         a = 16 * lane < vbytes ? ld16<(LM & kStream) != 0>(at(base, lo)) : make_uint4(0, 0, 0, 0);
         b = (lane < 20 && 1024 + 16 * lane < vbytes) ? ld16<(LM & kStream) != 0>(at(base, lo, 1024))
                                                       : make_uint4(0, 0, 0, 0);
         const int r = tile0 + 8 * lane;
         live = (LM & kFull) || r < V.np;
-        const uint32_t* ex = scalar_base(V.column_exps(col) + (tile0 >> 5));
         e = live ? *at(ex, lane_offset((uint32_t)lane >> 2 << 2)) : 0u;
     }
     __device__ __forceinline__ void codes(uint32_t* c) const {
@@ -500,12 +549,21 @@ struct Tile<CB_FRSZ2_GEN> {
         const unsigned char* base = scalar_base(V.column(col) + (int64_t)(tile0 >> 5) * (4 * L));
         // bytes of whole blocks below np (a piece that straddles their end
         // stays inside the column's 256-byte-rounded storage)
-        const int vbytes = ((LM & kFull) ? 16 : min(max((V.np - tile0) >> 5, 0), 16)) * 4 * L;
+        const int rows = (LM & kFull) ? kTile : tile_rows(V.np, tile0);
+        const int vbytes = (rows >> 5) * 4 * L;
         const uint32_t lo = lane_offset((uint32_t)lane * 16u);
+        const uint32_t* ex = scalar_base(V.column_exps(col) + (tile0 >> V.bs_log));
+        if constexpr ((LM & kBound) != 0) {
+            const Run run(base, (vbytes + 15) & ~15);
+            a = run.b16(lo);
+            b = run.b16(lo, 1024);
+            live = 1;  // (as frsz2_21's)
+            e = Run(ex, rows >> V.bs_log << 2).b4(lane_offset((uint32_t)lane >> (V.bs_log - 3) << 2));
+            return;
+        }
         a = 16 * lane < vbytes ? ld16<(LM & kStream) != 0>(at(base, lo)) : make_uint4(0, 0, 0, 0);
         b = 1024 + 16 * lane < vbytes ? ld16<(LM & kStream) != 0>(at(base, lo, 1024)) : make_uint4(0, 0, 0, 0);
         live = (LM & kFull) || tile0 + 8 * lane < V.np;
-        const uint32_t* ex = scalar_base(V.column_exps(col) + (tile0 >> V.bs_log));
         e = live ? *at(ex, lane_offset((uint32_t)lane >> (V.bs_log - 3) << 2)) : 0u;
     }
     __device__ __forceinline__ void codes(uint32_t* c) const {

@@ -57,6 +57,7 @@ enum EpiMode : int {
     EPI_FUSED_CHECK = 4,    // first update fused with the second projection:
                             // sums u_0..u_{ncols-2} and ||w||^2 (last column) ->
                             // step 7 test; u kept (h += u) only if it asks for it
+    EPI_PARTIALS = 5,       // none: the sums are formed by k_reduce
 };
 
 // Arnoldi steps between the progress reports of a cycle (Epi::prog).

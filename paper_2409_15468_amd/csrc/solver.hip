@@ -526,7 +526,8 @@ static int solve_impl(const cb_csr& A, const double* b, double* x, int m, double
                     // fused with the second projection: u is formed whether or
                     // not step 7 asks for it, and kept only if it does
                     ex.mode = EPI_FUSED_CHECK;
-                    launch_subtract_project(fmt, V, j + 1, hcol, wc, part, active, ex, s);
+                    launch_subtract_project(fmt, V, j + 1, hcol, wc, part, (W.L.part_s - W.L.part) / 8, active, ex,
+                                            s);
                 } else {
                     ex.mode = EPI_STEP_CHECK;
                     launch_subtract(fmt, V, j + 1, nullptr, hcol, wc, part, active, -1, ex, s);

@@ -59,12 +59,6 @@ constexpr int kStage = 512;             // nonzeros of a 64-row block staged in 
 constexpr int64_t kStreamBytes = (int64_t)192 << 20;  // columns that the Infinity Cache does not keep
 constexpr uint64_t kPollTicks = 200000000;  // 2 s of the 100 MHz counter
 
-// S.w holds the workgroup's rows of w by row, one double of padding per 8 so
-// that the lanes of a wave, which own 2, 4 or 8 consecutive rows each, read
-// their rows without bank conflicts.
-constexpr int kPadTile = kTile + kTile / 8;
-__device__ __forceinline__ int padded(int r) { return r + (r >> 3); }
-
 struct TeamShared {
     TeamArgs args;
     double red[kTW][kTC];   // per tile of the workgroup: column sums
@@ -77,7 +71,7 @@ struct TeamShared {
         double xch[kTW][8][64];  // the waves' parts of V h
         double prod[kTW][kStage];
     };
-    double w[kTW * kPadTile];
+    double w[kTW * kPadTile];  // the workgroup's rows of w (padded())
     State st;      // what the solve reports, kept by thread 0
     double carry;  // column j's entry after the old rotations
     int bad, dead;
@@ -310,24 +304,6 @@ constexpr int kSlotsOf = FMT == CB_F64 ? 2 : FMT == CB_FRSZ2_32 || FMT == CB_FRS
                      : is_generic<FMT> ? 3 : 8;
 // the wave's columns among the first jc
 __device__ __forceinline__ int columns_of(const Ctx& x, int jc) { return (jc - x.p + x.cs - 1) >> x.lcs; }
-// Makes the stored words opaque where they are used again: otherwise the
-// decoded values of one use are kept in registers for the next (16 registers a
-// column instead of 4 to 10), and spill.
-template <int FMT>
-__device__ __forceinline__ void opaque(Tile<FMT>& tl) {
-    constexpr int Q = sizeof(Tile<FMT>) / 16, W = sizeof(Tile<FMT>) % 16 / 4;
-    u32x4 q[Q];
-    uint32_t w[W + 1];
-    __builtin_memcpy(q, &tl, 16 * Q);
-    __builtin_memcpy(w, reinterpret_cast<const char*>(&tl) + 16 * Q, 4 * W);
-#pragma unroll
-    for (int i = 0; i < Q; ++i) asm volatile("" : "+v"(q[i]));
-#pragma unroll
-    for (int i = 0; i < W; ++i) asm volatile("" : "+v"(w[i]));
-    __builtin_memcpy(&tl, q, 16 * Q);
-    __builtin_memcpy(reinterpret_cast<char*>(&tl) + 16 * Q, w, 4 * W);
-}
-
 // S.red[t][c] = <D(v_c), w> over the tile for the wave's columns c < jc; the
 // columns in memory from the last to the first, the next 8 in flight while the
 // wave reduces the current ones, then the resident ones

@@ -276,5 +276,29 @@ __device__ __forceinline__ void subtract_tile(const BasisView& V, int j, const d
     }
 }
 
+// Rows of a tile in LDS, by row, with one double of padding per 8, so that the
+// lanes of a wave, which own 2, 4 or 8 consecutive rows each, read their rows
+// without bank conflicts.
+constexpr int kPadTile = kTile + kTile / 8;
+__device__ __forceinline__ int padded(int r) { return r + (r >> 3); }
+
+// Makes the stored words opaque where they are used again: otherwise the
+// decoded values of one use are kept in registers for the next (16 registers a
+// column instead of 4 to 10), and spill.
+template <int FMT>
+__device__ __forceinline__ void opaque(Tile<FMT>& tl) {
+    constexpr int Q = sizeof(Tile<FMT>) / 16, W = sizeof(Tile<FMT>) % 16 / 4;
+    u32x4 q[Q];
+    uint32_t w[W + 1];
+    __builtin_memcpy(q, &tl, 16 * Q);
+    __builtin_memcpy(w, reinterpret_cast<const char*>(&tl) + 16 * Q, 4 * W);
+#pragma unroll
+    for (int i = 0; i < Q; ++i) asm volatile("" : "+v"(q[i]));
+#pragma unroll
+    for (int i = 0; i < W; ++i) asm volatile("" : "+v"(w[i]));
+    __builtin_memcpy(&tl, q, 16 * Q);
+    __builtin_memcpy(reinterpret_cast<char*>(&tl) + 16 * Q, w, 4 * W);
+}
+
 }  // namespace dev
 }  // namespace cb

@@ -97,3 +97,13 @@ def test_fused_matches_separate_update_and_projection():
     np.testing.assert_allclose(w_a.cpu().numpy(), w_b.cpu().numpy(), rtol=0, atol=1e-13)
     np.testing.assert_allclose(out[:j].cpu().numpy(), u.cpu().numpy(), rtol=1e-11, atol=1e-13)
     assert abs(out[j].item() - norm2.item()) <= 1e-12 * norm2.item()
+
+
+@pytest.mark.parametrize("fmt", ["frsz2_32", "frsz2_16", "float64", "frsz2_12"])
+@pytest.mark.parametrize("n,j", [(31, 1), (513, 8), (513, 9), (545, 13), (1100000, 13), (1100000, 14), (545, 64), (545, 65),
+                                 (545, 104), (545, 105), (545, 300)])
+def test_columns_kept_in_registers(fmt, n, j):
+    """Around the numbers of columns that 1, 2, 4 and 8 waves keep in
+    registers, past them, with fewer columns than waves and with a last tile of
+    one block; 1100000 rows are enough tiles for one and two waves each."""
+    check(fmt, n, j, 7 * j + n % 97)
