@@ -162,8 +162,7 @@ int cb_basis_store(const cb_basis* V, int32_t col, const double* w, const double
 int cb_basis_load(const cb_basis* V, int32_t col, double* x, void* stream);
 
 /* Bytes of reduction workspace needed by the primitives below for n rows and
- * up to ncols columns: an 8 KB header (ticket counters that the call clears
- * itself) followed by per-workgroup partial sums.  Calls that share a
+ * up to ncols columns: an 8 KB header followed by per-workgroup partial sums.  Calls that share a
  * workspace must run in stream order. */
 int64_t cb_reduce_workspace_bytes(int32_t n, int32_t ncols);
 
@@ -183,8 +182,7 @@ int cb_cgs_project(const cb_basis* V, int32_t j, const double* w, double* h, voi
  * 1 <= j <= 513 fits), so the call allocates nothing.  The array's device
  * address is looked up on the first call on each device (that call may make
  * the HIP runtime load the library's code on the device); each device holds
- * its own copy until the process ends.  The call clears the array's ticket
- * counters itself with a fill kernel.  All calls on one device share the
+ * its own copy until the process ends.  All calls on one device share the
  * array: calls that may overlap on one device (different streams, or host
  * threads without stream order) race and give wrong results; calls in one
  * stream's order are safe.  CB_ERR_WORKSPACE if a call needed more than the

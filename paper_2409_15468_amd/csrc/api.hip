@@ -46,19 +46,21 @@ int64_t column_bytes(int f, int64_t n) {
 
 int64_t exponent_words(int f, int64_t n) { return frsz2_bits_of(f) ? padded_rows_of(f, n) >> block_log_of(f) : 0; }
 
-// Workspace of the primitives: a header holding the ticket counters of the
-// last-workgroup reduction, then the partial sums.
+// Workspace of the primitives: a header (its size is part of what callers
+// allocate), then the partial sums.
 int64_t reduce_workspace_bytes(int32_t n, int32_t ncols, int32_t nnz) {
     int64_t a = (int64_t)project_groups(n) * (ncols > 0 ? ncols : 1);
     int64_t b = nnz > 0 ? spmv_groups(n, nnz) : 0;
     return kCounterBytes + 8 * (a > b ? a : b);
 }
 
-static Epi store_epi(double* out, void* work) {
+// The primitives leave their partial sums to a second launch (launch_reduce).
+// The solver's way, ticket counters and the launch's last workgroup, needs the
+// counters cleared first, so it is two launches here too, and its tail of
+// dependent memory round trips is longer: 2 us of each 9 us call at n = 4101.
+static Epi partials_epi() {
     Epi e{};
-    e.mode = EPI_STORE;
-    e.out = out;
-    e.counter = static_cast<unsigned*>(work);
+    e.mode = EPI_PARTIALS;
     return e;
 }
 static double* partials_of(void* work) {
@@ -88,7 +90,7 @@ static int check_vec16(const void* a, const void* b = nullptr, const void* c = n
 
 // ----------------------------------------------------------------- projection without allocation
 // Reduction workspace of cb_cgs_project_noalloc: a file-scope device array
-// that covers every valid call (ticket counters, then kDotGroups partials for
+// that covers every valid call (the header, then kDotGroups partials for
 // each of up to kMaxRestart + 1 columns: 2.0 MiB).  Each GPU the library runs
 // on holds its own copy until the process ends.  Host code never names the
 // array in a launch: it takes the device address from hipGetSymbolAddress,
@@ -231,8 +233,8 @@ int cb_cgs_project(const cb_basis* V, int32_t j, const double* w, double* h, voi
         return fail(CB_ERR_WORKSPACE, "workspace %zu < %lld bytes", work_bytes,
                     (long long)reduce_workspace_bytes(V->n, j, 0));
     hipStream_t s = (hipStream_t)stream;
-    launch_zero_counter(static_cast<unsigned*>(work), s);
-    launch_project(V->format, *V, j, w, partials_of(work), nullptr, store_epi(h, work), s);
+    const int G = launch_project(V->format, *V, j, w, partials_of(work), nullptr, partials_epi(), s);
+    launch_reduce(partials_of(work), G, j, h, 0, nullptr, s);
     CB_HIP(hipGetLastError());
     return CB_OK;
 }
@@ -253,8 +255,8 @@ int cb_cgs_project_noalloc(const cb_basis* V, int32_t j, const double* w, double
     void* ws = scratch_on_current_device();
     if (!ws) return CB_ERR_HIP;
     hipStream_t s = (hipStream_t)stream;
-    launch_zero_counter(static_cast<unsigned*>(ws), s);  // a fill kernel, no memset node
-    launch_project(V->format, *V, j, w, partials_of(ws), nullptr, store_epi(h, ws), s);
+    const int G = launch_project(V->format, *V, j, w, partials_of(ws), nullptr, partials_epi(), s);
+    launch_reduce(partials_of(ws), G, j, h, 0, nullptr, s);
     CB_HIP(hipGetLastError());
     return CB_OK;
 }
@@ -270,9 +272,9 @@ int cb_cgs_subtract(const cb_basis* V, int32_t j, const double* h, double* w, do
         return fail(CB_ERR_WORKSPACE, "norm needs a workspace of %lld bytes",
                     (long long)reduce_workspace_bytes(V->n, 1, 0));
     hipStream_t s = (hipStream_t)stream;
-    if (norm2) launch_zero_counter(static_cast<unsigned*>(work), s);
-    launch_subtract(V->format, *V, j, nullptr, h, w, norm2 ? partials_of(work) : nullptr, nullptr, -1,
-                    store_epi(norm2, work), s);
+    double* part = norm2 ? partials_of(work) : nullptr;
+    const int G = launch_subtract(V->format, *V, j, nullptr, h, w, part, nullptr, -1, partials_epi(), s);
+    if (norm2) launch_reduce(part, G, 1, norm2, 0, nullptr, s);
     CB_HIP(hipGetLastError());
     return CB_OK;
 }
@@ -288,12 +290,10 @@ int cb_cgs_subtract_project(const cb_basis* V, int32_t j, const double* h, doubl
         return fail(CB_ERR_WORKSPACE, "workspace %zu < %lld bytes", work_bytes,
                     (long long)reduce_workspace_bytes(V->n, j + 1, 0));
     hipStream_t s = (hipStream_t)stream;
-    // two launches without the ticket counters, whose place the partial sums take too
-    Epi e{};
-    e.mode = EPI_PARTIALS;
+    // (the partial sums take the header's place too: a small n's tiles are more than its row groups)
     double* part = static_cast<double*>(work);
     const int G = launch_subtract_project(V->format, *V, j, h, w, part, reduce_workspace_bytes(V->n, j + 1, 0) / 8,
-                                          nullptr, e, s);
+                                          nullptr, partials_epi(), s);
     launch_reduce(part, G, j + 1, out, 0, nullptr, s);
     CB_HIP(hipGetLastError());
     return CB_OK;

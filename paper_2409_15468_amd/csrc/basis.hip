@@ -113,7 +113,7 @@ __global__ __launch_bounds__(kThreads) void k_project(BasisView V, int j,
         for (int k = 1; k < kThreads / 64; ++k) s += red[k][i];
         store_partial(partials + (int64_t)(c0 + i) * G + g, s);
     }
-    epilogue(e, partials, elds);
+    if (e.mode != EPI_PARTIALS) epilogue(e, partials, elds);
 }
 
 // ----------------------------------------------------------------- CGS update / x update
@@ -187,7 +187,7 @@ __global__ __launch_bounds__(kThreads) void k_subtract(BasisView V, int j, const
     if (partials) {
         const double t = block_sum<kThreads>(nrm);
         if (tid == 0) store_partial(partials + blockIdx.x, t);
-        epilogue(e, partials, elds);
+        if (e.mode != EPI_PARTIALS) epilogue(e, partials, elds);
     }
 }
 
@@ -420,10 +420,6 @@ __global__ void k_fill(double* __restrict__ x, double v, int64_t n) {
     default: { constexpr int F = CB_FRSZ2_32; KERNEL_CALL; break; }          \
     }
 
-__global__ void k_zero(unsigned* __restrict__ c, int words) {
-    for (int i = threadIdx.x; i < words; i += blockDim.x) c[i] = 0u;
-}
-
 // Non-temporal basis loads pay off once the columns one pass reads no longer
 // fit in the 256 MB Infinity Cache next to the rest of the working set; below
 // that, the solver's four passes per step over the same columns hit in it.
@@ -432,10 +428,6 @@ constexpr int kResidentWaves = 2048;
 static int streams_basis(const BasisView& b, int j) {
     constexpr int64_t kCacheResident = (int64_t)192 << 20;
     return (int64_t)j * (b.col_bytes + 4 * b.exp_stride) > kCacheResident;
-}
-
-void launch_zero_counter(unsigned* counter, hipStream_t s) {
-    k_zero<<<1, 256, 0, s>>>(counter, kCounterBytes / 4);
 }
 
 void launch_store(int fmt, const cb_basis& V, int col, const double* w, const double* divisor,
@@ -454,7 +446,7 @@ void launch_load(int fmt, const cb_basis& V, int col, double* x, hipStream_t s) 
     CB_DISPATCH(fmt, (k_load<F><<<grid, kThreads, 0, s>>>(b, col, x)));
 }
 
-void launch_project(int fmt, const cb_basis& V, int j, const double* w, double* partials,
+int launch_project(int fmt, const cb_basis& V, int j, const double* w, double* partials,
                     const int* guard, const Epi& e, hipStream_t s) {
     BasisView b = view_of(V);
     const int G = dot_groups(V.n);
@@ -479,9 +471,10 @@ void launch_project(int fmt, const cb_basis& V, int j, const double* w, double* 
     ee.cw = cw;
     const int stream = streams_basis(b, j);
     CB_DISPATCH(fmt, (k_project<F><<<grid, kThreads, 0, s>>>(b, j, w, partials, G, cw, stream, guard, ee)));
+    return G;
 }
 
-void launch_subtract(int fmt, const cb_basis& V, int j, const int* jdev, const double* h,
+int launch_subtract(int fmt, const cb_basis& V, int j, const int* jdev, const double* h,
                      double* w, double* partials, const int* guard, int sign, const Epi& e,
                      hipStream_t s) {
     BasisView b = view_of(V);
@@ -495,6 +488,7 @@ void launch_subtract(int fmt, const cb_basis& V, int j, const int* jdev, const d
     const int stream = streams_basis(b, j);
     CB_DISPATCH(fmt, (k_subtract<F, 4><<<grid, kThreads, 0, s>>>(b, j, jdev, h, w, partials, sign, stream,
                                                                 guard, ee)));
+    return G;
 }
 
 // Workgroups of `kernel` the current device holds at once (its occupancy per

@@ -164,20 +164,18 @@ void launch_store(int fmt, const cb_basis& V, int col, const double* w, const do
 void launch_load(int fmt, const cb_basis& V, int col, double* x, hipStream_t s);
 // h = V^T w: partials[c * G + g] for c < j, then the epilogue e (its counter
 // must read 0) forms and uses the sums.
-void launch_project(int fmt, const cb_basis& V, int j, const double* w, double* partials,
+int launch_project(int fmt, const cb_basis& V, int j, const double* w, double* partials,
                     const int* guard, const Epi& e, hipStream_t s);
 // w += sign * V h (h device); with partials != NULL also ||w||^2 per
 // workgroup and the epilogue e on it.
-void launch_subtract(int fmt, const cb_basis& V, int j, const int* jdev, const double* h,
+int launch_subtract(int fmt, const cb_basis& V, int j, const int* jdev, const double* h,
                      double* w, double* partials, const int* guard, int accumulate_sign,
                      const Epi& e, hipStream_t s);
 // w -= V h (h device, j coefficients), then partials of u = V^T w (c < j) and
 // ||w||^2 (c = j), and the epilogue e (FUSED_CHECK).
-// (capacity: doubles of `partials`; returns the partials per column, which
-// EPI_PARTIALS leaves to launch_reduce)
+// (capacity: doubles of `partials`)
 int launch_subtract_project(int fmt, const cb_basis& V, int j, const double* h, double* w, double* partials,
                             int64_t capacity, const int* guard, const Epi& e, hipStream_t s);
-void launch_zero_counter(unsigned* counter, hipStream_t s);
 // Stage 2: out[c] (op 0: =, op 1: +=) = sum_g partials[c * G + g], c < ncols.
 void launch_reduce(const double* partials, int G, int ncols, double* out, int op,
                    const int* guard, hipStream_t s);
