@@ -233,8 +233,10 @@ int cb_cgs_project(const cb_basis* V, int32_t j, const double* w, double* h, voi
         return fail(CB_ERR_WORKSPACE, "workspace %zu < %lld bytes", work_bytes,
                     (long long)reduce_workspace_bytes(V->n, j, 0));
     hipStream_t s = (hipStream_t)stream;
-    const int G = launch_project(V->format, *V, j, w, partials_of(work), nullptr, partials_epi(), s);
-    launch_reduce(partials_of(work), G, j, h, 0, nullptr, s);
+    if (!launch_project_column(V->format, *V, j, w, h, s)) {
+        const int G = launch_project(V->format, *V, j, w, partials_of(work), nullptr, partials_epi(), s);
+        launch_reduce(partials_of(work), G, j, h, 0, nullptr, s);
+    }
     CB_HIP(hipGetLastError());
     return CB_OK;
 }
@@ -255,8 +257,10 @@ int cb_cgs_project_noalloc(const cb_basis* V, int32_t j, const double* w, double
     void* ws = scratch_on_current_device();
     if (!ws) return CB_ERR_HIP;
     hipStream_t s = (hipStream_t)stream;
-    const int G = launch_project(V->format, *V, j, w, partials_of(ws), nullptr, partials_epi(), s);
-    launch_reduce(partials_of(ws), G, j, h, 0, nullptr, s);
+    if (!launch_project_column(V->format, *V, j, w, h, s)) {
+        const int G = launch_project(V->format, *V, j, w, partials_of(ws), nullptr, partials_epi(), s);
+        launch_reduce(partials_of(ws), G, j, h, 0, nullptr, s);
+    }
     CB_HIP(hipGetLastError());
     return CB_OK;
 }

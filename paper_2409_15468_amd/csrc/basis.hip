@@ -116,6 +116,38 @@ __global__ __launch_bounds__(kThreads) void k_project(BasisView V, int j,
     if (e.mode != EPI_PARTIALS) epilogue(e, partials, elds);
 }
 
+// The projection of a short vector in one launch: workgroup c forms
+// h[c] = <D(v_c), w> over all rows, wave p of it over the tiles p, p + 8, ....
+// Nothing is left to sum, so it spares the caller the second launch, which at
+// these sizes costs more than the work.
+template <int FMT>
+__global__ __launch_bounds__(512) void k_project_column(BasisView V, const double* __restrict__ w,
+                                                        double* __restrict__ h) {
+    __shared__ double part[8];
+    const int lane = threadIdx.x & 63, wave = wave_index(), ntiles = (V.np + kTile - 1) / kTile;
+    double s = 0.0;
+    for (int t = wave; t < ntiles; t += 16) {
+        // two tiles in flight (of one past the last nothing is read)
+        Tile<FMT> a, b;
+        double wa[8], wb[8];
+        const int ta = t * kTile, tb = min(t + 8, ntiles) * kTile;
+        a.template load<kBound>(V, blockIdx.x, ta, lane);
+        b.template load<kBound>(V, blockIdx.x, tb, lane);
+        load_rows<FMT>(w, ta, lane, V.n, wa);
+        load_rows<FMT>(w, tb, lane, V.n, wb);
+        s += a.dot(wa);
+        s += b.dot(wb);
+    }
+    s = wave_sum(s);
+    if (lane == 0) part[wave] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double sum = part[0];
+        for (int k = 1; k < 8; ++k) sum += part[k];
+        h[blockIdx.x] = sum;
+    }
+}
+
 // ----------------------------------------------------------------- CGS update / x update
 // Start of the update kernels: the guard, the device-side count jdev (if any;
 // the host's j then bounds it) and the coefficients h[0 .. j) are loaded
@@ -217,13 +249,12 @@ constexpr int sub_proj_threads(int W) { return W == 8 ? 512 : 256; }
 // with frsz2_32 and 255 with float64; this 92 and 156 (at 2^21 x 12 43 and 65,
 // now 34 and 42).  The formats whose decoding bounds them gain less, since each
 // column is still decoded twice (frsz2_21 at 10^6 x 100 103 -> 93).
-template <int FMT, int W>
+template <int FMT, int W, int N>
 __global__ __launch_bounds__(sub_proj_threads(W), 2) void k_subtract_project(BasisView V, int j,
                                                                           const double* __restrict__ h,
                                                                           double* __restrict__ w,
                                                                           double* __restrict__ partials,
                                                                           const int* __restrict__ guard, Epi e) {
-    constexpr int N = kResidentColumns<FMT>;
     constexpr int NW = sub_proj_threads(W) / 64, T = NW / W;  // waves, tiles at a time
     constexpr int S = 8 / W;                                  // values of a lane's 8 that are a wave's share
     constexpr int B = W == 1 ? 1 : 2;
@@ -425,6 +456,11 @@ __global__ void k_fill(double* __restrict__ x, double v, int64_t n) {
 // that, the solver's four passes per step over the same columns hit in it.
 constexpr int kResidentWaves = 2048;
 
+// Rows up to which the projection runs a column per workgroup: a call takes 8.5
+// us against 11.5 of the two launches from 1000 to 32768 rows, 11 against 12 at
+// 65536, 20 against 12 at 131072 (17 and 100 columns alike).
+constexpr int kColumnRows = 1 << 15;
+
 static int streams_basis(const BasisView& b, int j) {
     constexpr int64_t kCacheResident = (int64_t)192 << 20;
     return (int64_t)j * (b.col_bytes + 4 * b.exp_stride) > kCacheResident;
@@ -474,6 +510,13 @@ int launch_project(int fmt, const cb_basis& V, int j, const double* w, double* p
     return G;
 }
 
+bool launch_project_column(int fmt, const cb_basis& V, int j, const double* w, double* h, hipStream_t s) {
+    if (V.n > kColumnRows) return false;
+    BasisView b = view_of(V);
+    CB_DISPATCH(fmt, (k_project_column<F><<<j, 512, 0, s>>>(b, w, h)));
+    return true;
+}
+
 int launch_subtract(int fmt, const cb_basis& V, int j, const int* jdev, const double* h,
                      double* w, double* partials, const int* guard, int sign, const Epi& e,
                      hipStream_t s) {
@@ -495,7 +538,7 @@ int launch_subtract(int fmt, const cb_basis& V, int j, const int* jdev, const do
 // CU times the CU count), cached per device and kernel; 0 if the runtime
 // cannot say.
 static int resident_groups(const void* kernel, int id, int threads) {
-    constexpr int kDevs = 16, kIds = 64;
+    constexpr int kDevs = 16, kIds = 80;
     static std::atomic<int> cache[kDevs][kIds];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kDevs || id < 0 || id >= kIds) return 0;
@@ -511,13 +554,13 @@ static int resident_groups(const void* kernel, int id, int threads) {
 }
 
 // capacity: doubles of `partials`.
-template <int FMT, int W>
+template <int FMT, int W, int N>
 static int run_subtract_project(const BasisView& b, int j, const double* h, double* w, double* partials,
                                 int64_t capacity, const int* guard, Epi e, hipStream_t s) {
     constexpr int threads = sub_proj_threads(W), T = threads / 64 / W;
     const int ngroups = ((b.np + kTile - 1) / kTile + T - 1) / T;
-    const int R = resident_groups(reinterpret_cast<const void*>(&k_subtract_project<FMT, W>),
-                                  FMT * 4 + (W > 1) + (W > 2) + (W > 4), threads);
+    const int R = resident_groups(reinterpret_cast<const void*>(&k_subtract_project<FMT, W, N>),
+                                  FMT * 5 + (W > 1) + (W > 2) + (W > 4) + (N < kResidentColumns<FMT> ? 4 : 0), threads);
     int64_t G = R > 0 ? R : 256;
     if (G > capacity / (j + 1)) G = capacity / (j + 1);
     if (G > kTicketGroup * kMaxTicketGroups) G = kTicketGroup * kMaxTicketGroups;
@@ -527,7 +570,7 @@ static int run_subtract_project(const BasisView& b, int j, const double* h, doub
     e.G = (int)G;
     e.ncols = j + 1;  // u_0 .. u_{j-1} and the norm
     e.cw = j + 1;
-    k_subtract_project<FMT, W><<<(unsigned)G, threads, 0, s>>>(b, j, h, w, partials, guard, e);
+    k_subtract_project<FMT, W, N><<<(unsigned)G, threads, 0, s>>>(b, j, h, w, partials, guard, e);
     return (int)G;
 }
 
@@ -550,10 +593,14 @@ int launch_subtract_project(int fmt, const cb_basis& V, int j, const double* h, 
                 W = v;
             }
         }
-        if (W == 1) G = run_subtract_project<F, 1>(b, j, h, w, partials, capacity, guard, e, s);
-        else if (W == 2) G = run_subtract_project<F, 2>(b, j, h, w, partials, capacity, guard, e, s);
-        else if (W == 4) G = run_subtract_project<F, 4>(b, j, h, w, partials, capacity, guard, e, s);
-        else G = run_subtract_project<F, 8>(b, j, h, w, partials, capacity, guard, e, s);
+        // few columns in fewer registers, where a third workgroup then fits a CU
+        // (frsz2_16 in the n = 2^21 inner solve: 18.6 -> 17.6 us a step)
+        constexpr int Few = N > 13 ? 8 : N;
+        if (W == 1 && j <= Few) G = run_subtract_project<F, 1, Few>(b, j, h, w, partials, capacity, guard, e, s);
+        else if (W == 1) G = run_subtract_project<F, 1, N>(b, j, h, w, partials, capacity, guard, e, s);
+        else if (W == 2) G = run_subtract_project<F, 2, N>(b, j, h, w, partials, capacity, guard, e, s);
+        else if (W == 4) G = run_subtract_project<F, 4, N>(b, j, h, w, partials, capacity, guard, e, s);
+        else G = run_subtract_project<F, 8, N>(b, j, h, w, partials, capacity, guard, e, s);
     }));
     return G;
 }

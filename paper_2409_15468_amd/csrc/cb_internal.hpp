@@ -164,6 +164,8 @@ void launch_store(int fmt, const cb_basis& V, int col, const double* w, const do
 void launch_load(int fmt, const cb_basis& V, int col, double* x, hipStream_t s);
 // h = V^T w: partials[c * G + g] for c < j, then the epilogue e (its counter
 // must read 0) forms and uses the sums.
+// h = V^T w in one launch, for short vectors (false: not launched)
+bool launch_project_column(int fmt, const cb_basis& V, int j, const double* w, double* h, hipStream_t s);
 int launch_project(int fmt, const cb_basis& V, int j, const double* w, double* partials,
                     const int* guard, const Epi& e, hipStream_t s);
 // w += sign * V h (h device); with partials != NULL also ||w||^2 per

@@ -141,3 +141,14 @@ def test_generic_width_tiles(bits, n):
     cb.cb_cgs_subtract(V, j, torch.from_numpy(h).cuda(), wd)
     err = np.abs(wd.cpu().numpy() - oracle.cgs_subtract(dec, h, w))
     assert np.all(err <= 1e-14 * (np.abs(w) + np.abs(dec) @ np.abs(h)))
+
+
+@pytest.mark.parametrize("fmt", ["frsz2_32", "frsz2_21", "frsz2_16", "float64", "frsz2_12", "frsz2b64_32"])
+@pytest.mark.parametrize("n,j", [(1, 1), (512, 3), (4097, 2), (32768, 5), (32769, 5)])
+def test_project_of_short_vectors(fmt, n, j):
+    """A column per workgroup up to 32768 rows: one row, one tile, one tile
+    more than the workgroup's waves, the longest, and one row past it."""
+    V, _, dec = build_basis(fmt, n, j, seed=n + j)
+    w = np.random.default_rng(j).standard_normal(n)
+    h = cb.cb_cgs_project(V, j, torch.from_numpy(w).cuda()).cpu().numpy()
+    assert np.all(np.abs(h - oracle.cgs_project(dec, w)) <= 1e-12 * (np.abs(dec).T @ np.abs(w)) + 1e-300)
