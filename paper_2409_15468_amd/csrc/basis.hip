@@ -420,6 +420,63 @@ __global__ __launch_bounds__(sub_proj_threads(W), 2) void k_subtract_project(Bas
     if (e.mode != EPI_PARTIALS) epilogue(e, partials, lds.epi);
 }
 
+// The same for the few columns of a solver step's start, each read twice, the
+// second time from the cache: one wave per tile and no registers held.  In a
+// solve the data come from HBM behind the SpMV, and what counts is how soon
+// the loads go out.
+// At most 256 registers (two waves per SIMD): with one, a launch of more
+// workgroups than CUs runs in two rounds and pays its start-up twice.
+template <int FMT, int U>
+__global__ __launch_bounds__(kThreads, 2) void k_subtract_project_few(BasisView V, int j,
+                                                               const double* __restrict__ h,
+                                                               double* __restrict__ w,
+                                                               double* __restrict__ partials,
+                                                               const int* __restrict__ guard, Epi e) {
+    __shared__ double elds[kEpiLds];
+    __shared__ double hc[kMaxRestart + 1];
+    __shared__ double red[kThreads / 64][kMaxRestart + 2];
+    __shared__ double stage[kThreads / 64][kTile];
+    const int go = load_coefficients(guard, nullptr, h, j, hc);
+    if (!go) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = wave_index();
+    const int G = gridDim.x;
+    const int ngroups = row_groups_dev(V.np);
+    for (int i = lane; i < j; i += 64) red[wave][i] = 0.0;
+    __syncthreads();
+    double nrm = 0.0;
+    for (int rg = blockIdx.x; rg < ngroups; rg += G) {
+        const int tile0 = rg * kRowsPerWG + wave * kTile;
+        double acc[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) acc[q] = 0.0;
+        const bool full = tile0 + kTile <= V.np;
+        if (full) subtract_tile<FMT, U, kFull>(V, j, hc, tile0, lane, acc);
+        else subtract_tile<FMT, U, 0>(V, j, hc, tile0, lane, acc);
+        double wv[8];
+        load_rows<FMT>(w, tile0, lane, V.n, wv);
+        double t = 0.0;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            wv[q] = wv[q] - acc[q];
+            t = fma(wv[q], wv[q], t);  // rows >= n hold 0
+        }
+        nrm += t;
+        store_rows_lds<FMT>(w, tile0, lane, V.n, wv, stage[wave]);
+        if (full) project_tile_narrow<FMT, kFull>(V, 0, j, tile0, lane, wv, red[wave]);
+        else project_tile_narrow<FMT, 0>(V, 0, j, tile0, lane, wv, red[wave]);
+    }
+    const double wn = wave_sum(nrm);
+    if (lane == 0) red[wave][j] = wn;
+    __syncthreads();
+    for (int i = tid; i <= j; i += kThreads) {
+        double s = red[0][i];
+#pragma unroll
+        for (int k = 1; k < kThreads / 64; ++k) s += red[k][i];
+        store_partial(partials + (int64_t)i * G + blockIdx.x, s);
+    }
+    epilogue(e, partials, elds);
+}
+
 // ----------------------------------------------------------------- stage 2
 __global__ __launch_bounds__(256) void k_reduce(const double* __restrict__ partials, int G,
                                                 double* __restrict__ out, int op,
@@ -538,7 +595,7 @@ int launch_subtract(int fmt, const cb_basis& V, int j, const int* jdev, const do
 // CU times the CU count), cached per device and kernel; 0 if the runtime
 // cannot say.
 static int resident_groups(const void* kernel, int id, int threads) {
-    constexpr int kDevs = 16, kIds = 80;
+    constexpr int kDevs = 16, kIds = 96;
     static std::atomic<int> cache[kDevs][kIds];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kDevs || id < 0 || id >= kIds) return 0;
@@ -552,6 +609,12 @@ static int resident_groups(const void* kernel, int id, int threads) {
     if (r > 0) cache[dev][id].store(r, std::memory_order_relaxed);
     return r;
 }
+
+// Columns up to which the solver's launches read them twice: an inner solve of 11
+// steps on n = 2^21 banded rows, frsz2_16, refined to 1e-12, takes 10.39 ms so and
+// 10.53 by the one-read kernel; the n = 10^6 GMRES(100) 59.5 ms either way.
+// (The primitive's launches, hot in the cache, are faster read once at any count.)
+constexpr int kFewColumns = 12;
 
 // capacity: doubles of `partials`.
 template <int FMT, int W, int N>
@@ -578,6 +641,20 @@ int launch_subtract_project(int fmt, const cb_basis& V, int j, const double* h, 
                             int64_t capacity, const int* guard, const Epi& e, hipStream_t s) {
     BasisView b = view_of(V);
     int G = 0;
+    if (e.mode != EPI_PARTIALS && j <= kFewColumns) {
+        G = project_groups(V.n);
+        CB_DISPATCH(fmt, ({
+            // whole waves of resident workgroups
+            const int R = resident_groups(reinterpret_cast<const void*>(&k_subtract_project_few<F, 4>), 80 + F, kThreads);
+            if (R > 0 && G > R) G = G / R * R;
+            Epi ee = e;
+            ee.G = G;
+            ee.ncols = j + 1;
+            ee.cw = j + 1;
+            k_subtract_project_few<F, 4><<<G, kThreads, 0, s>>>(b, j, h, w, partials, guard, ee);
+        }));
+        return G;
+    }
     CB_DISPATCH(fmt, ({
         constexpr int N = kResidentColumns<F>;
         // among the W whose waves hold the columns (8 if none does) the one with
