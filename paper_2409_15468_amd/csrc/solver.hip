@@ -229,6 +229,9 @@ struct Pinned {
     }
 };
 static thread_local Pinned g_pinned;
+// The words that a caller of solve_impl keeps over inner solves: g_pinned grows,
+// and moves, with what each of those asks for.
+static thread_local Pinned g_pinned_outer;
 
 static double now_s() {
     return std::chrono::duration<double>(std::chrono::steady_clock::now().time_since_epoch()).count();
@@ -717,7 +720,7 @@ int cbgmres_ir_solve(const cb_csr* A, const double* b, double* x, int32_t m, dou
     double* d = reinterpret_cast<double*>(W.base + W.L.total + vec);
     double* scal = reinterpret_cast<double*>(W.base + W.L.total + 2 * vec);
     double* part = W.at<double>(W.L.part);
-    double* hv = static_cast<double*>(g_pinned.get(sizeof(State) + (size_t)m * 8 + 64));
+    double* hv = static_cast<double*>(g_pinned_outer.get(64));
     int status = CB_ERR_NOT_CONVERGED;
     cb_result acc;
     memset(&acc, 0, sizeof acc);
@@ -870,7 +873,7 @@ int cbgmres_solve_auto(const cb_csr* A, const double* b, double* x, int32_t m, d
     // ||b|| and ||b - A x0||
     W.L = layout_of(n, m, candidates_host[0]);
     double* part = W.at<double>(W.L.part);
-    double* hv = static_cast<double*>(g_pinned.get(sizeof(State) + (size_t)std::max(m, probe_steps) * 8 + 64));
+    double* hv = static_cast<double*>(g_pinned_outer.get(64));
     if (!hv) return fail(CB_ERR_HIP, "hipHostMalloc failed");
     enqueue_sumsq(b, n, part, scal, s);
     launch_spmv(*A, x, b, xp, part, 1, nullptr, s);

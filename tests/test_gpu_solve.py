@@ -4,6 +4,8 @@ iteration count is within 2% of the oracle's, the error against the
 FP64-basis oracle is reported, and the edge cases of the method behave as the
 oracle does (b = 0, A = I, x0 exact, caps, non-finite input, tiny and ragged
 n, GMRES(1)).  Solves are deterministic run to run."""
+import threading
+
 import numpy as np
 import pytest
 
@@ -189,6 +191,34 @@ def test_iterative_refinement_other_inner_formats(fmt, inner_tol):
     assert res["restarts"] == ref.outer
     assert within_2pct(res["iterations"], ref.iterations)
     assert np.linalg.norm(x - ref.x) / np.linalg.norm(ref.x) < 1e-10
+
+
+@pytest.mark.parametrize("fmt,m", [("frsz2_16", 40), ("frsz2_32", 40)])
+def test_iterative_refinement_of_short_rows_in_a_fresh_thread(fmt, m):
+    """A 5-point system: its inner solves ask for more pinned host memory than
+    the refinement itself, in a thread that has none yet, and the outer
+    residuals that decide convergence are read after them."""
+    s = synth.plain_2d(N=48, seed=3)
+    ref = oracle.ir_solve(s.A, s.b, m, 1e-4, 1e-12, fmt)
+    got = {}
+
+    def refine():
+        A = cb.DeviceCSR.from_host(s.A.row_ptr, s.A.col, s.A.val)
+        x = torch.zeros(s.A.n, dtype=torch.float64, device="cuda")
+        got["res"] = cb.cbgmres_ir_solve(A, torch.from_numpy(s.b).cuda(), x, m, 1e-4, 1e-12, fmt)
+        got["x"] = x.cpu().numpy()
+
+    t = threading.Thread(target=refine)
+    t.start()
+    t.join()
+    res, x = got["res"], got["x"]
+    print(fmt, res["restarts"], res["iterations"], "| oracle", ref.outer, ref.iterations)
+    assert res["converged"] and ref.converged and res["restarts"] > 2
+    rel = host_rrn(s.A, s.b, x)
+    # (the rounding of b - A x itself is a few eps ||A|| ||x|| / ||b||: below 1e-14)
+    assert rel <= 1e-12 + 1e-14 and abs(rel - res["rel_residual"]) <= 1e-14
+    assert res["restarts"] == ref.outer
+    assert within_2pct(res["iterations"], ref.iterations)
 
 
 def test_tall_system_short_restart():
