@@ -274,7 +274,7 @@ __device__ __forceinline__ void finish_step(const Epi& e, int breakdown, double 
         }
     }
     __syncthreads();
-    for (int i = threadIdx.x; i <= j + 1; i += blockDim.x) h[i] = lh[i];
+    for (int i = threadIdx.x; i <= j + 1; i += kThreads) h[i] = lh[i];
 }
 
 // LDS (doubles) the epilogue needs: the column sums, or H column j with the
@@ -316,7 +316,7 @@ __device__ __forceinline__ bool reduce_tickets(const Epi& e, double* partials, d
     for (int a = c0; a < c1; a += 256) {
         const int nc = min(256, c1 - a);
         reduce_range(partials, G, m0, gsize, 1, a, nc, lds);
-        for (int i = threadIdx.x; i < nc; i += blockDim.x) store_partial(partials + (int64_t)(a + i) * G + m0, lds[i]);
+        for (int i = threadIdx.x; i < nc; i += kThreads) store_partial(partials + (int64_t)(a + i) * G + m0, lds[i]);
         __syncthreads();
     }
     __builtin_amdgcn_s_waitcnt(0);
@@ -335,7 +335,7 @@ __device__ __forceinline__ void reduce_final(const Epi& e, const double* partial
     reduce_range(partials, e.G, 0, ng, kTicketGroup, a, nc, lds);
 }
 
-// sum of p[0 .. G) in a fixed order, valid in thread 0 (blockDim.x == 256):
+// sum of p[0 .. G) in a fixed order, valid in thread 0 (kThreads = 256 threads):
 // thread t adds p[t], p[t + 256], ... in order, eight loads in flight at a
 // time, then the threads are summed with block_sum.
 __device__ __forceinline__ double sum_partials(const double* __restrict__ p, int G) {
@@ -418,8 +418,10 @@ __device__ __forceinline__ void step_logic(const Epi& e, double t, double* lds, 
     if (do_finish) finish_step(e, bd, hn_s, z, lds, p);
 }
 
-// Run by every workgroup of the launch after its partials are written
-// (all threads; blockDim.x == 256).
+// Run by every workgroup of the launch after its partials are written, by
+// kThreads = 256 threads of it: all of them, or the first ones of a wider
+// workgroup whose other waves have ended (blockDim.x says the latter's width, so
+// nothing here steps by it).
 __device__ __forceinline__ void epilogue(const Epi& e, double* partials, double* lds) {
     if (!reduce_tickets(e, partials, lds)) return;
     Pre p;

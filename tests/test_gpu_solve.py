@@ -234,6 +234,25 @@ def test_tall_system_short_restart():
     np.testing.assert_allclose(x, b / 2, rtol=1e-13)
 
 
+@pytest.mark.parametrize("fmt,m", [("frsz2_32", 300), ("float64", 300), ("frsz2_32", 200)])
+def test_long_cycle_of_fused_steps(fmt, m):
+    """One cycle of 200 and 300 steps, fused, of which none (float64) or three
+    ask for the second pass: past step 256 the rotated column of H has more
+    rows than the fused kernel's last workgroup has threads left.  Without the
+    second pass the iterate moves by 2e-9 (frsz2_32) or 1e-14 (float64) under
+    last-bit changes of b and by 4e-4 when the steps from 257 on are left out;
+    within 1e-6 of the oracle's."""
+    s = synth.plain_2d(N=160, seed=3)
+    kw = dict(eta=1e-3, max_iters=m)
+    res, x, hist = gpu_solve(s.A, s.b, m, 1e-10, fmt, fuse_updates=2, history_cap=m, **kw)
+    ref = oracle.gmres(s.A, s.b, m, 1e-10, fmt, hist_cap=m, **kw)
+    assert res["iterations"] == m == ref.iterations and res["restarts"] == 1
+    assert res["reorths"] == ref.reorths
+    assert np.linalg.norm(x - ref.x) <= 1e-6 * np.linalg.norm(ref.x)
+    np.testing.assert_allclose(hist, ref.history, rtol=1e-3)
+    np.testing.assert_allclose(res["rel_residual"], ref.rel_residual, rtol=1e-2)
+
+
 @pytest.mark.parametrize("fmt", ["frsz2_21", "float32", "float64"])
 @pytest.mark.parametrize("fuse", [1, 2])
 def test_fused_and_separate_first_update(fmt, fuse):
