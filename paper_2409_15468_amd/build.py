@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libcbgmres.so")
 SOURCES = ["api.hip", "basis.hip", "spmv.hip", "solver.hip", "team.hip", "team_batch.hip", "team_ring.hip", "batch.hip", "intensity.hip", "server.cpp"]
-HEADERS = ["cb_internal.hpp", "codec.hpp", "reduce.hpp", "epilogue.hpp", "tiles.hpp", "team.hpp", "team_solve.hpp"]
+HEADERS = ["cb_internal.hpp", "codec.hpp", "reduce.hpp", "epilogue.hpp", "tiles.hpp", "team.hpp", "team_solve.hpp", "ring_claim.hpp"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",

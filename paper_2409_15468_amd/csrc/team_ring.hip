@@ -41,6 +41,7 @@
 #include <vector>
 
 #include "cb_internal.hpp"
+#include "ring_claim.hpp"
 #include "team.hpp"
 #include "team_solve.hpp"
 
@@ -51,7 +52,6 @@ using namespace dev;
 namespace {
 
 constexpr int kRingUnits = 1 << 16;  // units published and unclaimed at most (a power of two)
-constexpr uint64_t kClosed = UINT64_C(1) << 63;
 constexpr int kRingPatience = 10;    // a team may wait 20 s for workgroups that finish other systems
 
 struct RingDesc {
@@ -89,25 +89,30 @@ __device__ __forceinline__ void copy_in(const T* __restrict__ src, T* __restrict
     for (int64_t i = i0 + threadIdx.x; i < i1; i += kTeamThreads) dst[i] = ld_sys(src + i);
 }
 
+struct ClaimMemory {
+    const RingCtl* ctl;
+    uint64_t* h;
+    __device__ __forceinline__ uint64_t head() const {
+        const uint64_t v = ld_ctl(h);
+        __builtin_amdgcn_s_waitcnt(0);  // the tail's load goes out after this one's value is here
+        return v;
+    }
+    __device__ __forceinline__ uint32_t tail() const { return ld_sys(&ctl->tail); }
+    __device__ __forceinline__ uint32_t unit(uint32_t i) const { return ld_sys(&ctl->units[i & (kRingUnits - 1)]); }
+    __device__ __forceinline__ bool stop() const { return ld_sys(&ctl->stop) != 0; }
+    __device__ __forceinline__ bool cas(uint64_t from, uint64_t to) const {
+        return atomicCAS(reinterpret_cast<unsigned long long*>(h), from, to) == from;
+    }
+};
+
 // The next unit (slot | rank << 16), or -1 once the launch is closed.
 __device__ int claim(const RingCtl* ctl, uint64_t* head, int idle_polls, uint64_t t_start, uint64_t slice) {
+    ClaimMemory m{ctl, head};
     for (int idle = 0;;) {
-        const unsigned t = ld_sys(&ctl->tail);
-        const uint64_t h = ld_ctl(head);
-        if (h & kClosed) return -1;
-        const bool work = (int)(t - (unsigned)h) > 0;
-        const unsigned unit = work ? ld_sys(&ctl->units[(unsigned)h & (kRingUnits - 1)]) : 0u;
-        // between systems: nothing published is unclaimed, or a team's first unit is next
-        const bool between = !work || (unit >> 16) == 0;
         const bool late = __builtin_amdgcn_s_memrealtime() - t_start >= slice;
-        if (work && !(late && between)) {
-            if (atomicCAS(reinterpret_cast<unsigned long long*>(head), h, h + 1) == h) return (int)unit;
-            continue;  // another workgroup took it: look again at once
-        }
-        if (late || idle >= idle_polls || ld_sys(&ctl->stop)) {
-            atomicCAS(reinterpret_cast<unsigned long long*>(head), h, h | kClosed);
-            continue;  // closed now, or the counter has moved on
-        }
+        const int r = claim_step(m, late, idle >= idle_polls);
+        if (r >= 0 || r == kClaimClosed) return r;
+        if (r == kClaimAgain) continue;  // look again at once
         __builtin_amdgcn_s_sleep(127);  // ~8k cycles between polls of the bus
         ++idle;
     }
@@ -121,7 +126,7 @@ __device__ __attribute__((noinline)) void ring_solve(int rank) {
     team_solve<FMT, kSlotsOf<FMT>>(rank, S);
 }
 
-__global__ void k_ring_open(uint64_t* head) { *head = ld_ctl(head) & ~kClosed; }
+__global__ void k_ring_open(uint64_t* head) { *head = ld_ctl(head) & ~kRingClosed; }
 
 __global__ __launch_bounds__(kTeamThreads, 2) void k_team_ring(const RingDesc* __restrict__ descs, RingCtl* ctl,
                                                                uint64_t* head, unsigned* arrived, int idle_polls,
