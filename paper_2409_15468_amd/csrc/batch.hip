@@ -416,7 +416,7 @@ double now_s() {
 }
 
 // One workgroup per system, for the systems of `which`: where a team does not
-// fit the GPU or did not come together.
+// fit the GPU or did not come together (x is as it was on entry).
 int solve_one_group_each(const std::vector<BatchItem>& all, const std::vector<int>& which, const BatchOpts& o,
                          cb_result* results_host, hipStream_t s) {
     const int count = (int)which.size();
@@ -471,6 +471,7 @@ int solve_by_teams(const cb_batch_item* items, int count, const BatchOpts& o, cb
         a.eta = o.eta;
         a.max_iters = o.max_iters;
         a.literal = o.literal;
+        a.wait_us = team_wait_us();
         ll_words += team_ll_words(a.G, a.m);
     }
     if (order.empty()) return CB_OK;
@@ -500,7 +501,7 @@ int solve_by_teams(const cb_batch_item* items, int count, const BatchOpts& o, cb
     CB_HIP(hipMallocAsync(reinterpret_cast<void**>(&mem), (size_t)total, s));
     int64_t at = 0;
     for (int i : order) {
-        args[i].ll = reinterpret_cast<uint64_t*>(mem + o_ll) + at;
+        team_exchange(args[i], reinterpret_cast<uint64_t*>(mem + o_ll) + at);
         args[i].st = reinterpret_cast<State*>(mem + o_st) + i;
         at += team_ll_words(args[i].G, args[i].m);
     }
@@ -532,7 +533,10 @@ int solve_by_teams(const cb_batch_item* items, int count, const BatchOpts& o, cb
     }
     for (int i : order) {
         if (st != CB_OK) break;
-        if (states[i].status == kTeamAbandoned) left.push_back(i);
+        if (states[i].status == kTeamLost &&
+            hipMemcpyAsync(items[i].x, args[i].x0, (size_t)args[i].n * 8, hipMemcpyDeviceToDevice, s) != hipSuccess)
+            st = fail(CB_ERR_HIP, "batch: restoring x failed");
+        if (states[i].status == kTeamAbandoned || states[i].status == kTeamLost) left.push_back(i);
         else fill_result(&results_host[i], states[i], 0.0);
     }
     return st;
@@ -557,6 +561,7 @@ TeamArgs team_batch_args(const cb_batch_item& q) {
     a.V = view_of(V);
     a.col_total = a.V.col_bytes + 4 * a.V.exp_stride;
     a.w = reinterpret_cast<double*>(ws + lay.w);
+    a.x0 = reinterpret_cast<double*>(ws + lay.v);  // (the one-workgroup kernel's v)
     a.tol = q.tol;
     a.n = q.A.n;
     a.m = q.m;

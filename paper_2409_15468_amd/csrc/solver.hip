@@ -88,8 +88,16 @@ __global__ void k_sumsq(const double* __restrict__ x, int n, double* __restrict_
     if (threadIdx.x == 0) partials[blockIdx.x] = s;
 }
 
+// What a solve counts on from: nothing, or the cycles that launches of a team
+// have done before the rest of the solve is left to the launch-per-kernel path.
+struct Carry {
+    int32_t iters, cycles, reorths, breakdowns;
+    double basis_bytes;
+    int64_t recorded;  // entries of the history
+};
+
 __global__ void k_init(State* st, int32_t* flag, unsigned* counter, double tol, double eta, int max_iters,
-                       int literal) {
+                       int literal, Carry from) {
     for (int i = threadIdx.x; i < kCounterBytes / 4; i += blockDim.x) counter[i] = 0u;
     if (threadIdx.x != 0) return;
     State z = {};
@@ -98,6 +106,11 @@ __global__ void k_init(State* st, int32_t* flag, unsigned* counter, double tol, 
     z.eta = eta;
     z.max_iters = max_iters;
     z.literal = literal;
+    z.iters = from.iters;
+    z.cycles = from.cycles;
+    z.reorths = from.reorths;
+    z.breakdowns = from.breakdowns;
+    z.basis_bytes = from.basis_bytes;
     z.rel = -1.0;
     z.gabs = -1.0;
     if (z.nb == 0.0) {
@@ -319,20 +332,21 @@ void fill_result(cb_result* res, const State& hs, double seconds) {
 }
 
 // The solve by one team of resident workgroups (team.hip), which the matrix's
-// short rows, n and m allow.  Returns a cb_status, or kTeamAbandoned when the
-// team could not run (x is then still a valid start).  The exchange slots take
-// the place of w2 (or of the partial sums, for the smallest systems) and the
-// history of a launch that of H, so the workspace is that of the other path.
+// short rows, n and m allow.  Returns a cb_status, or kTeamAbandoned when there is
+// no team for it or no launch of one (more) could run: x is then what *done says
+// has been done of the solve.  The exchange slots take the place of w2 (or of the
+// partial sums, for the smallest systems) and the history of a launch, if the
+// caller wants one, that of H, so the workspace is that of the other path.
 static int solve_team(const cb_csr& A, const double* b, double* x, int m, int fmt, const Ws& W, const TeamArgs& opts,
                       const double* dinv, const double* pval, double* history_host, int64_t history_cap,
-                      cb_result* res, double t0, hipStream_t s) {
+                      cb_result* res, double t0, Carry* done, hipStream_t s) {
     const int n = A.n, cap = team_device_groups();
     TeamShape sh;
     if (spmv_lanes_per_row(n, A.nnz) != 0 || !team_shape(n, m, cap, &sh)) return kTeamAbandoned;
     const int64_t ll_bytes = 8 * team_ll_words(sh.G, m);
     TeamArgs a = opts;
-    if (ll_bytes <= W.L.vals - W.L.w2) a.ll = W.at<uint64_t>(W.L.w2);
-    else if (ll_bytes <= W.L.plan - W.L.part) a.ll = W.at<uint64_t>(W.L.part);
+    if (ll_bytes <= W.L.vals - W.L.w2) team_exchange(a, W.at<uint64_t>(W.L.w2));
+    else if (ll_bytes <= W.L.plan - W.L.part) team_exchange(a, W.at<uint64_t>(W.L.part));
     else return kTeamAbandoned;
     const cb_basis V{fmt, n, m + 1, 0, W.base + W.L.vals, frsz2_bits_of(fmt) ? W.at<uint32_t>(W.L.exps) : nullptr};
     a.rp = A.row_ptr;
@@ -346,28 +360,36 @@ static int solve_team(const cb_csr& A, const double* b, double* x, int m, int fm
     a.col_total = a.V.col_bytes + 4 * a.V.exp_stride;
     a.w = W.at<double>(W.L.w);
     a.st = W.at<State>(W.L.state);
-    a.hist = W.at<double>(W.L.H);
-    a.hist_cap = (m + 1) * m;
+    const bool history = history_host && history_cap > 0;
+    a.hist = history ? W.at<double>(W.L.H) : nullptr;
+    a.hist_cap = history ? (m + 1) * m : INT32_MAX - 2 * kTeamMaxRestart;
     a.n = n;
     a.m = m;
     a.G = sh.G;
     a.cs = sh.cs;
     a.resume = 0;
-    State* hs = static_cast<State*>(g_pinned.get(sizeof(State) + (size_t)a.hist_cap * 8));
+    State* hs = static_cast<State*>(g_pinned.get(sizeof(State) + (history ? (size_t)a.hist_cap * 8 : 0)));
     if (!hs) return fail(CB_ERR_HIP, "hipHostMalloc failed");
     double* hh = reinterpret_cast<double*>(hs + 1);
-    int64_t recorded = 0;
+    int64_t& recorded = done->recorded;
     TeamSeats seats(sh.G, cap);
     seats.wait();
     for (;;) {
+        a.wait_us = team_wait_us();
         launch_team(fmt, a, s);
         CB_HIP(hipGetLastError());
         CB_HIP(hipMemcpyAsync(hs, a.st, sizeof(State), hipMemcpyDeviceToHost, s));
-        const bool keep = history_host && recorded < history_cap;
+        const bool keep = history && recorded < history_cap;
         if (keep) CB_HIP(hipMemcpyAsync(hh, a.hist, (size_t)a.hist_cap * 8, hipMemcpyDeviceToHost, s));
         CB_HIP(hipStreamSynchronize(s));
         if (hs->status == kTeamAbandoned) return kTeamAbandoned;
+        done->iters = hs->iters;
+        done->cycles = hs->cycles;
+        done->reorths = hs->reorths;
+        done->breakdowns = hs->breakdowns;
+        done->basis_bytes = hs->basis_bytes;
         for (int k = 0; keep && k < hs->steps && recorded < history_cap; ++k) history_host[recorded++] = hh[k] / hs->nb;
+        if (hs->status == kTeamLost) return kTeamAbandoned;
         if (hs->stop) break;
         a.resume = 1;
     }
@@ -392,6 +414,7 @@ static int solve_impl(const cb_csr& A, const double* b, double* x, int m, double
     const int literal = opt ? opt->literal_breakdown : 0;
     const int fuse_opt = opt ? opt->fuse_updates : 0;
 
+    Carry from{};
     {
         TeamArgs o{};
         o.tol = tol;
@@ -399,7 +422,7 @@ static int solve_impl(const cb_csr& A, const double* b, double* x, int m, double
         o.max_iters = max_iters;
         o.max_cycles = max_cycles;
         o.literal = literal;
-        const int r = solve_team(A, b, x, m, fmt, W, o, dinv, pval, history_host, history_cap, res, t0, s);
+        const int r = solve_team(A, b, x, m, fmt, W, o, dinv, pval, history_host, history_cap, res, t0, &from, s);
         if (r != kTeamAbandoned) return r;
     }
 
@@ -458,11 +481,11 @@ static int solve_impl(const cb_csr& A, const double* b, double* x, int m, double
     State* hs = static_cast<State*>(g_pinned.get(sizeof(State) + (size_t)m * 8));
     if (!hs) return fail(CB_ERR_HIP, "hipHostMalloc failed");
     double* hh = reinterpret_cast<double*>(reinterpret_cast<unsigned char*>(hs) + sizeof(State));
-    int64_t recorded = 0;
+    int64_t recorded = from.recorded;
 
     // ||b||, tolerances, counters
     enqueue_sumsq(b, n, part, &st->r2, s);
-    k_init<<<1, 256, 0, s>>>(st, flag, counter, tol, eta, max_iters, literal);
+    k_init<<<1, 256, 0, s>>>(st, flag, counter, tol, eta, max_iters, literal, from);
     CB_HIP(hipMemcpyAsync(hs, st, sizeof(State), hipMemcpyDeviceToHost, s));
     CB_HIP(hipStreamSynchronize(s));
     if (hs->stop) {
@@ -562,7 +585,7 @@ static int solve_impl(const cb_csr& A, const double* b, double* x, int m, double
             }
             CB_HIP(hipGetLastError());
             ++cycles;
-            if (max_cycles > 0 && cycles >= max_cycles) {
+            if (max_cycles > 0 && from.cycles + cycles >= max_cycles) {
                 CB_HIP(hipMemcpyAsync(hs, st, sizeof(State), hipMemcpyDeviceToHost, s));
                 CB_HIP(hipMemcpyAsync(hh, hist, (size_t)m * 8, hipMemcpyDeviceToHost, s));
                 CB_HIP(hipStreamSynchronize(s));

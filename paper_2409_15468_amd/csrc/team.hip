@@ -106,7 +106,13 @@ bool team_shape(int32_t n, int32_t m, int capacity, TeamShape* s) {
 }
 
 int64_t team_ll_words(int G, int m) {
-    return G <= kDirect ? (int64_t)4 * G * (m + 2) : (int64_t)2 * (G + 1) * (m + 2);
+    return kJoinWords + (G <= kDirect ? (int64_t)4 * G * (m + 2) : (int64_t)2 * (G + 1) * (m + 2));
+}
+
+static thread_local int32_t g_wait_us = -1, g_wait_skip = 0;
+int32_t team_wait_us() {
+    if (g_wait_us < 0 || g_wait_skip-- > 0) return kTeamWaitUs;
+    return g_wait_us;
 }
 
 void launch_team_clear(uint64_t* ll, int64_t words, hipStream_t s) {
@@ -114,7 +120,7 @@ void launch_team_clear(uint64_t* ll, int64_t words, hipStream_t s) {
 }
 
 void launch_team(int fmt, const TeamArgs& a, hipStream_t s) {
-    launch_team_clear(a.ll, team_ll_words(a.G, a.m), s);
+    launch_team_clear(reinterpret_cast<uint64_t*>(a.join), team_ll_words(a.G, a.m), s);
 #define CB_TEAM_CASE(F)                                                                    \
     case F:                                                                                \
         if (a.cs >= 4) k_team<F, kSlotsOf<F>><<<a.G, kTeamThreads, 0, s>>>(a);              \
@@ -136,3 +142,12 @@ void launch_team(int fmt, const TeamArgs& a, hipStream_t s) {
 }
 
 }  // namespace cb
+
+// How long the teams of this host thread's solves wait for their workgroups, in
+// microseconds (negative: the default), from the launch after the next
+// `launches` on.  With 0 no team forms, and the tests reach the paths that solve
+// such systems.
+extern "C" void cb_internal_team_wait(int32_t us, int32_t launches) {
+    cb::g_wait_us = us;
+    cb::g_wait_skip = launches;
+}

@@ -8,8 +8,20 @@ namespace cb {
 constexpr int kTeamThreads = 512;
 constexpr int kTeamMaxRestart = 104;  // R, the rotations and the sums of a step sit in LDS
 constexpr int kTeamMaxGroups = 256;   // one workgroup per CU
-// State::status of a solve whose workgroups did not find each other in time
+// State::status of a solve whose workgroups did not come together: nothing but
+// this word has been written
 constexpr int kTeamAbandoned = -1;
+// ... and of one in which a workgroup that had come was not heard of for 20 s
+// (its queue was taken off the GPU): x holds each row before or after the last
+// cycle's update, the counters are those of the cycles before
+constexpr int kTeamLost = -2;
+// How long a team may take to come together before its solve goes the other
+// way: longer than any kernel of this library that may be in its way, at the
+// sizes that fit the GPU's memory many times (a projection of 2^24 x 101 takes 1
+// ms), short against what a caller whose GPU never has room would wait for each
+// solve.
+constexpr int32_t kTeamWaitUs = 100000;
+constexpr int kJoinWords = 16;  // ahead of the exchange slots, in a line of its own
 
 struct State;
 
@@ -23,7 +35,9 @@ struct TeamArgs {
     const double* dinv;  // Jacobi preconditioner, or NULL
     BasisView V;
     double* w;           // n doubles: the vector the next SpMV reads
-    uint64_t* ll;        // exchange slots, team_ll_words of them
+    uint64_t* ll;        // exchange slots
+    unsigned* join;      // workgroups that have come; top bit: the team does not form
+    double* x0;          // NULL, or n doubles that get x as it was on entry
     State* st;
     double* hist;        // NULL, or |g_{j+1}| per step of this launch
     double tol, eta;
@@ -33,7 +47,7 @@ struct TeamArgs {
     int32_t hist_cap;    // entries of hist; the launch ends when a cycle may not fit
     int32_t resume;      // the counters continue from *st
     int32_t format;      // basis format (launches of many systems)
-    int32_t patience;    // 2 s units a poll waits before the solve is abandoned (0: one)
+    int32_t wait_us;     // the team's workgroups come within this time or not at all (0: not at all)
     uint32_t epoch0;     // tags of this solve are above it; the slots hold none that are
 };
 
@@ -46,7 +60,15 @@ int team_device_groups();
 // The team for n rows and restart length m; false if it does not fit.
 bool team_shape(int32_t n, int32_t m, int capacity, TeamShape* s);
 int64_t team_ll_words(int G, int m);
-// Clear the slots and start the team on stream s.
+// a.join and a.ll in team_ll_words words at p.
+inline void team_exchange(TeamArgs& a, uint64_t* p) {
+    a.join = reinterpret_cast<unsigned*>(p);
+    a.ll = p + kJoinWords;
+}
+// kTeamWaitUs, or what cb_internal_team_wait has set for the next launch of this
+// host thread.
+int32_t team_wait_us();
+// Clear the words at a.join and start the team on stream s.
 void launch_team(int fmt, const TeamArgs& a, hipStream_t s);
 // The team for one of many systems; depends on its rows only.
 TeamShape team_batch_shape(int32_t n);

@@ -52,7 +52,7 @@ using namespace dev;
 namespace {
 
 constexpr int kRingUnits = 1 << 16;  // units published and unclaimed at most (a power of two)
-constexpr int kRingPatience = 10;    // a team may wait 20 s for workgroups that finish other systems
+constexpr int32_t kRingWaitUs = 20000000;  // a team may wait for workgroups that finish other systems
 
 struct RingDesc {
     TeamArgs a;
@@ -179,6 +179,7 @@ __global__ __launch_bounds__(kTeamThreads, 2) void k_team_ring(const RingDesc* _
             const unsigned n = __hip_atomic_fetch_add(&arrived[slot], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
             if (n == (unsigned)D.a.G - 1u) {
                 __hip_atomic_store(&arrived[slot], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(D.a.join, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __hip_atomic_store(&ctl->served_by[slot], launch_id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
                 __hip_atomic_store(&ctl->done[slot], (unsigned)D.seq + 1u, __ATOMIC_RELEASE,
                                    __HIP_MEMORY_SCOPE_SYSTEM);
@@ -281,9 +282,9 @@ int ring_publish(BatchRing* r, const cb_batch_item& q, const int32_t* h_row_ptr,
     d.a = team_batch_args(q);
     d.a.eta = 0.7071067811865476;
     d.a.max_iters = 20000;
-    d.a.ll = ll;
+    team_exchange(d.a, ll);
     d.a.st = r->results_dev + slot;
-    d.a.patience = kRingPatience;
+    d.a.wait_us = team_wait_us() == 0 ? 0 : kRingWaitUs;
     d.a.epoch0 = r->epoch[slot];
     d.h_row_ptr = h_row_ptr;
     d.h_col = h_col;
@@ -312,10 +313,12 @@ bool ring_poll(BatchRing* r, uint32_t seq, cb_result* res, uint32_t* launch) {
     const State& st = r->results[slot];
     if (res) {
         fill_result(res, st, 0.0);
-        if (st.status == kTeamAbandoned) res->status = CB_ERR_HIP;
+        if (st.status == kTeamAbandoned || st.status == kTeamLost) res->status = CB_ERR_HIP;
     }
-    // (an abandoned team may have used tags past those its first workgroup reports)
-    r->epoch[slot] = st.status == kTeamAbandoned ? UINT32_MAX : (uint32_t)st.pad0;
+    // (a lost team may have used tags past those its first workgroup reports, one
+    // that never formed has used none)
+    if (st.status == kTeamLost) r->epoch[slot] = UINT32_MAX;
+    else if (st.status != kTeamAbandoned) r->epoch[slot] = (uint32_t)st.pad0;
     if (launch) *launch = r->ctl->served_by[slot];
     r->free_slots.push_back(slot);
     return true;

@@ -33,11 +33,15 @@
 // content has gone on (a workgroup takes part in an exchange only after it has
 // read the one before; the direct form alternates between two sets of slots).
 //
-// All polls end: a poll that has waited two seconds marks the solve as
-// abandoned and the workgroup leaves; the others follow at their own limit and
-// the host runs the solve with the launch-per-kernel path.  The host keeps the
-// team's workgroups within the GPU's CUs over all solves in flight (one
-// workgroup fills a CU's registers), so this needs other programs on the GPU.
+// A workgroup first waits until the whole team is on the GPU (gather).  The host
+// keeps the teams in flight within the GPU's CUs (one workgroup fills a CU's
+// registers), so only other programs' work can keep a team from forming; after
+// wait_us it then leaves as one, before it has written anything, and the host
+// solves the system by a path that needs no team.  Behind the gather every
+// workgroup runs, and a poll waits for the others' work only.  Its limit of 20 s
+// ends the launch where the GPU takes the team off its CUs for that long: a
+// workgroup whose poll expires tags what it still sends with 0, for which nobody
+// waits, so no sum that lacks a part is ever used.
 #pragma once
 
 #include "cb_internal.hpp"
@@ -57,7 +61,8 @@ constexpr int kTC = kTM + 2;            // columns of one exchange at most
 constexpr int kDirect = 32;             // workgroups up to which everyone reads all partials
 constexpr int kStage = 512;             // nonzeros of a 64-row block staged in LDS
 constexpr int64_t kStreamBytes = (int64_t)192 << 20;  // columns that the Infinity Cache does not keep
-constexpr uint64_t kPollTicks = 200000000;  // 2 s of the 100 MHz counter
+constexpr uint64_t kPollTicks = 2000000000;  // 20 s of the 100 MHz counter
+constexpr unsigned kNoTeam = 1u << 31;      // in the join word
 
 struct TeamShared {
     TeamArgs args;
@@ -108,11 +113,10 @@ __device__ __forceinline__ void ll_store(uint64_t* s, double v, uint32_t tag) {
     __hip_atomic_store(s, t | lo32(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(s + 1, t | hi32(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// Waits for K slots at once (those with live[k]); false after two seconds (or
-// args.patience times that).
+// Waits for K slots at once (those with live[k]); after kPollTicks the team is
+// lost, and S.dead says so.
 template <int K>
-__device__ __forceinline__ bool ll_load(const Ctx& x, const uint64_t* const* s, const bool* live, uint32_t tag,
-                                        double* v) {
+__device__ __forceinline__ bool ll_load(const Ctx& x, const uint64_t* const* s, const bool* live, uint32_t tag, double* v) {
     uint64_t t_end = 0;
     for (unsigned it = 0;; ++it) {
         uint64_t a[K], b[K];
@@ -130,21 +134,53 @@ __device__ __forceinline__ bool ll_load(const Ctx& x, const uint64_t* const* s, 
         if (ok) return true;
         if ((it & 255u) == 255u) {
             const uint64_t now = __builtin_amdgcn_s_memrealtime();
-            if (t_end == 0) t_end = now + kPollTicks * (uint64_t)max(1, x.S.args.patience);
-            else if (now > t_end) return false;
+            if (t_end == 0) t_end = now + kPollTicks;
+            else if (now > t_end) {
+                x.S.dead = 1;
+                return false;
+            }
         }
     }
 }
 
+// True once all G workgroups of the team are on the GPU; false, in every one of
+// them, if they are not within wait_us (all threads).  The count and the
+// decision against the team share a word: a workgroup gives up by setting the top
+// bit of a count that is not full, and a count with that bit is never full.
+__device__ __forceinline__ bool gather(Ctx& x) {
+    if (threadIdx.x == 0) {
+        unsigned* join = x.arg(&TeamArgs::join);
+        const int us = x.arg(&TeamArgs::wait_us);
+        if (us <= 0) __hip_atomic_fetch_or(join, kNoTeam, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        unsigned v = __hip_atomic_fetch_add(join, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
+        const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
+        while (v != (unsigned)x.G && !(v & kNoTeam)) {
+            if (__builtin_amdgcn_s_memrealtime() - t0 > (uint64_t)us * 100u) {
+                if (__hip_atomic_compare_exchange_strong(join, &v, v | kNoTeam, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                         __HIP_MEMORY_SCOPE_AGENT))
+                    v |= kNoTeam;
+                continue;  // (else v is the word as it now is)
+            }
+            __builtin_amdgcn_s_sleep(1);
+            v = ld_ctl(join);
+        }
+        x.S.dead = v & kNoTeam ? 1 : 0;
+    }
+    __syncthreads();
+    return uniform(x.S.dead) == 0;
+}
+
 // tot[c] = sum over the team of red[.][c], c < nc: post sends the workgroup's
 // sums, collect waits for the team's (all threads; synchronised on return;
-// false: the solve is abandoned).  Rows published before post are visible to
+// false: the team is lost, and nothing the workgroup sends from then on counts).  Rows published before post are visible to
 // every workgroup after collect.
 __device__ __forceinline__ uint64_t* slots(const Ctx& x) {
     const bool two_sets = x.G <= kDirect;
     return x.arg(&TeamArgs::ll) + (two_sets ? (int64_t)(x.epoch & 1u) * 2 * x.G * (x.m + 2) : 0);
 }
-__device__ __forceinline__ void post(Ctx& x, int nc) {
+// (of a workgroup that has lost the team, one that nobody waits for)
+__device__ __forceinline__ uint32_t tag_of(const Ctx& x) { return x.S.dead ? 0u : x.epoch; }
+__device__ __forceinline__ void post(Ctx& x, int nc, bool may_be_lost) {
     TeamShared& S = x.S;
     const int tid = threadIdx.x, G = x.G, ncs = x.m + 2;
     __builtin_amdgcn_s_waitcnt(0);  // this wave's published rows have arrived
@@ -152,18 +188,18 @@ __device__ __forceinline__ void post(Ctx& x, int nc) {
     ++x.epoch;
     uint64_t* ll = slots(x);
     if (tid < nc) {
+        const uint32_t tag = may_be_lost ? tag_of(x) : x.epoch;
         double s = S.red[0][tid];
         for (int k = 1; k < x.R; ++k) s += S.red[k][tid];
         if (G == 1) S.tot[tid] = s;
-        else if (G <= kDirect) ll_store(ll + 2 * ((int64_t)x.rank * ncs + tid), s, x.epoch);
-        else ll_store(ll + 2 * ((int64_t)tid * G + x.rank), s, x.epoch);
+        else if (G <= kDirect) ll_store(ll + 2 * ((int64_t)x.rank * ncs + tid), s, tag);
+        else ll_store(ll + 2 * ((int64_t)tid * G + x.rank), s, tag);
     }
 }
 __device__ __forceinline__ bool collect(Ctx& x, int nc) {
     TeamShared& S = x.S;
     const int tid = threadIdx.x, G = x.G, ncs = x.m + 2;
     uint64_t* ll = slots(x);
-    bool ok = true;
     if (G > 1 && G <= kDirect) {
         // wave q adds the partials of workgroups q, q + 8, ... in order, then
         // the waves' sums are added in order
@@ -179,14 +215,13 @@ __device__ __forceinline__ bool collect(Ctx& x, int nc) {
                     live[k] = g < G;
                     s[k] = ll + 2 * ((int64_t)g * ncs + c);
                 }
-                ok = ll_load<K>(x, s, live, x.epoch, v) && ok;
+                ll_load<K>(x, s, live, x.epoch, v);
                 double sum = 0.0;
 #pragma unroll
                 for (int k = 0; k < K; ++k) sum += live[k] ? v[k] : 0.0;
                 S.part[x.wave][c] = sum;
             }
         }
-        if (!ok) S.dead = 1;
         __syncthreads();
         if (tid < nc) {
             double s = S.part[0][tid];
@@ -199,14 +234,15 @@ __device__ __forceinline__ bool collect(Ctx& x, int nc) {
             const uint64_t* s[1] = {ll + 2 * ((int64_t)c * G + tid)};
             const bool live[1] = {tid < G};
             double v[1];
-            ok = ll_load<1>(x, s, live, x.epoch, v) && ok;
+            ll_load<1>(x, s, live, x.epoch, v);
             const double q = wave_sum(live[0] ? v[0] : 0.0);
             if (x.lane == 0) S.part[x.wave][0] = q;
             __syncthreads();
             if (tid == 0) {
+                const uint32_t tag = tag_of(x);
                 double t = S.part[0][0];
                 for (int k = 1; k < kTW; ++k) t += S.part[k][0];
-                ll_store(out + 2 * c, t, x.epoch);
+                ll_store(out + 2 * c, t, tag);
             }
             __syncthreads();
         }
@@ -214,10 +250,9 @@ __device__ __forceinline__ bool collect(Ctx& x, int nc) {
             const uint64_t* s[1] = {out + 2 * tid};
             const bool live[1] = {true};
             double v[1];
-            ok = ll_load<1>(x, s, live, x.epoch, v) && ok;
+            ll_load<1>(x, s, live, x.epoch, v);
             S.tot[tid] = v[0];
         }
-        if (!ok) S.dead = 1;
     }
     __syncthreads();
     return uniform(S.dead) == 0;
@@ -451,9 +486,17 @@ __device__ __forceinline__ void team_solve(int rank, TeamShared& S) {
     x.p = x.wave & (x.cs - 1);
     x.tile0 = (rank * x.R + x.t) * kTile;
     x.full = x.tile0 + kTile <= x.arg(&TeamArgs::V).np;
-    if (tid == 0) {
-        S.bad = 0;
-        S.dead = 0;
+    if (tid == 0) S.bad = 0;
+    if (!gather(x)) {
+        if (rank == 0 && tid == 0) x.arg(&TeamArgs::st)->status = kTeamAbandoned;
+        return;
+    }
+    if (double* x0 = x.arg(&TeamArgs::x0)) {
+        const double* xv = x.arg(&TeamArgs::x);
+        for (int i = tid; i < x.R * kTile; i += kTeamThreads) {
+            const int r = rank * x.R * kTile + i;
+            if (r < x.n) x0[r] = ld_ctl(xv + r);
+        }
     }
     int iters = 0, cycles = 0, status = CB_OK, stop = 0, recorded = 0;
     double nb = 0.0;
@@ -463,6 +506,8 @@ __device__ __forceinline__ void team_solve(int rank, TeamShared& S) {
         cycles = uniform(ld_ctl(&st->cycles));
         if (tid == 0) {
             S.st = State{};
+            S.st.iters = iters;
+            S.st.cycles = cycles;
             S.st.reorths = ld_ctl(&st->reorths);
             S.st.breakdowns = ld_ctl(&st->breakdowns);
             S.st.basis_bytes = ld_ctl(&st->basis_bytes);
@@ -574,7 +619,9 @@ __device__ __forceinline__ void team_solve(int rank, TeamShared& S) {
                 asm volatile("" : "+v"(x.lane));
                 put_sumsq(x, wv, jc);
                 team_project<FMT, N>(x, rs, jc, wv, stream);
-                post(x, jc + 1);
+                post(x, jc + 1, false);
+                // (lost: the exchange below fails in its turn; a way out of both loops
+                // from here costs them 40 registers)
                 if (!collect(x, jc + 1)) break;
                 const double t = sqrt(uniform(S.tot[jc]));
                 if (tid < jc) {
@@ -614,7 +661,7 @@ __device__ __forceinline__ void team_solve(int rank, TeamShared& S) {
         if (phase == kStep || phase == kResidual) publish<FMT>(x, x.arg(&TeamArgs::w));
         put_sumsq(x, wv, 0);
         if (x.p == 0 && x.lane == 0) S.red[x.t][1] = x.t == 0 && S.bad ? 1.0 : 0.0;
-        post(x, 2);
+        post(x, 2, true);
         // while the sums travel: the entries of the next SpMV, and by one
         // thread the old rotations on column j (steps 15-16)
         load_entries(x, x.arg(phase == kStep || phase == kResidual ? &TeamArgs::aval : &TeamArgs::val), x.wave, ent);
@@ -641,7 +688,7 @@ __device__ __forceinline__ void team_solve(int rank, TeamShared& S) {
             S.carry = carry;
         }
         if (!collect(x, 2)) {
-            status = kTeamAbandoned;
+            status = kTeamLost;
             break;
         }
         const double norm = sqrt(uniform(S.tot[0]));
@@ -683,6 +730,10 @@ __device__ __forceinline__ void team_solve(int rank, TeamShared& S) {
             }
             // (or no room for a cycle's history: the next launch goes on)
             if (stop || recorded + x.m > x.arg(&TeamArgs::hist_cap)) break;
+            if (tid == 0) {
+                S.st.iters = iters;
+                S.st.cycles = cycles;
+            }
             cycles += 1;
             for (int i = tid; i <= x.m; i += kTeamThreads) S.g[i] = i == 0 ? norm : 0.0;
             d = norm;
@@ -757,8 +808,10 @@ __device__ __forceinline__ void team_solve(int rank, TeamShared& S) {
     if (rank != 0) return;
     if (tid == 0) {
         S.st.nb = nb;
-        S.st.iters = iters;
-        S.st.cycles = cycles;
+        if (status != kTeamLost) {
+            S.st.iters = iters;
+            S.st.cycles = cycles;
+        }
         S.st.stop = stop;
         S.st.status = status;
         S.st.steps = recorded;
