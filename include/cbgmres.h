@@ -435,7 +435,9 @@ int cb_intensity_run(const cb_basis* V, int32_t col, int32_t ops, double a, doub
  * solve; a launch holds as many teams as fit the GPU.  A system's result does
  * not depend on the rest of the batch (the team and its reduction order follow
  * from the system's rows); it may differ in the last bits from cbgmres_solve
- * on the same system, whose reductions are ordered otherwise.
+ * on the same system, whose reductions are ordered otherwise.  (A system whose
+ * team does not come together within 0.1 s, because other programs' work holds
+ * the GPU's CUs, is solved by one workgroup, as if no team had been tried.)
  * ====================================================================== */
 typedef struct cb_batch_item {
     cb_csr A;                /* device CSR, 1 <= n <= cbgmres_batch_max_n() */
@@ -488,7 +490,9 @@ int cbgmres_solve_batch(const cb_batch_item* items, int32_t count, const cb_opti
  * included.  Arrival order is kept within each kind; small requests do not
  * wait behind large ones.  The path depends on a request's shape only and
  * neither path's arithmetic depends on the other requests, so a result is the
- * same, bit for bit, alone and in any mix.
+ * same, bit for bit, alone and in any mix.  (Where other programs' work on the
+ * GPU keeps a team of workgroups from coming together, within 0.1 s, the request
+ * is solved without one and may differ in the last bits.)
  * ====================================================================== */
 typedef struct cb_server cb_server;
 

@@ -451,6 +451,16 @@ int solve_one_group_each(const std::vector<BatchItem>& all, const std::vector<in
     return st;
 }
 
+BatchItem item_of(const cb_batch_item& q) {
+    unsigned char* ws = static_cast<unsigned char*>(q.workspace);
+    const BatchLayout lay = batch_layout(q.A.n, q.m, q.format);
+    return BatchItem{q.A.row_ptr, q.A.col, q.A.val, q.b, q.x, ws + lay.vals,
+                     frsz2_bits_of(q.format) ? reinterpret_cast<uint32_t*>(ws + lay.exps) : nullptr,
+                     reinterpret_cast<double*>(ws + lay.v), reinterpret_cast<double*>(ws + lay.w),
+                     column_bytes(q.format, q.A.n), exponent_words(q.format, q.A.n),
+                     q.A.n, q.A.nnz, q.m, q.format, q.tol};
+}
+
 // The systems by teams of workgroups, in as few launches as fit the GPU: the
 // longest systems first, so that the systems of a launch take about as long.
 // Appends to `left` those that have to take the other path.
@@ -546,6 +556,16 @@ int solve_by_teams(const cb_batch_item* items, int count, const BatchOpts& o, cb
 
 int64_t batch_workspace_bytes(int32_t n, int32_t m, int format) { return batch_layout(n, m, format).total; }
 
+int batch_without_teams(const cb_batch_item* items, int count, cb_result* results, hipStream_t s) {
+    std::vector<BatchItem> d;
+    std::vector<int> which;
+    for (int i = 0; i < count; ++i) {
+        d.push_back(item_of(items[i]));
+        which.push_back(i);
+    }
+    return solve_one_group_each(d, which, BatchOpts{kDefaultEta, kDefaultMaxIters, 0}, results, s);
+}
+
 TeamArgs team_batch_args(const cb_batch_item& q) {
     unsigned char* ws = static_cast<unsigned char*>(q.workspace);
     const BatchLayout lay = batch_layout(q.A.n, q.m, q.format);
@@ -613,17 +633,11 @@ static int solve_batch(const cb_batch_item* items, int32_t count, const cb_optio
         if ((int64_t)q.workspace_bytes < batch_workspace_bytes(q.A.n, q.m, q.format))
             return fail(CB_ERR_WORKSPACE, "batch item %d: workspace %zu < %lld bytes", i, q.workspace_bytes,
                         (long long)batch_workspace_bytes(q.A.n, q.m, q.format));
-        unsigned char* ws = static_cast<unsigned char*>(q.workspace);
-        const BatchLayout lay = batch_layout(q.A.n, q.m, q.format);
-        d[i] = BatchItem{q.A.row_ptr, q.A.col, q.A.val, q.b, q.x, ws + lay.vals,
-                         frsz2_bits_of(q.format) ? reinterpret_cast<uint32_t*>(ws + lay.exps) : nullptr,
-                         reinterpret_cast<double*>(ws + lay.v), reinterpret_cast<double*>(ws + lay.w),
-                         column_bytes(q.format, q.A.n), exponent_words(q.format, q.A.n),
-                         q.A.n, q.A.nnz, q.m, q.format, q.tol};
+        d[i] = item_of(q);
     }
     BatchOpts o;
-    o.eta = (opt && opt->eta > 0) ? opt->eta : 0.7071067811865476;
-    o.max_iters = (opt && opt->max_iters > 0) ? opt->max_iters : 20000;
+    o.eta = (opt && opt->eta > 0) ? opt->eta : kDefaultEta;
+    o.max_iters = (opt && opt->max_iters > 0) ? opt->max_iters : kDefaultMaxIters;
     o.literal = opt ? opt->literal_breakdown : 0;
     std::vector<int> left;
     int st = solve_by_teams(items, count, o, results_host, left, s);

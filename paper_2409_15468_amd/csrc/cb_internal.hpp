@@ -33,6 +33,8 @@ constexpr int kThreads = 256;     // threads per workgroup in the row kernels
 constexpr int kRowsPerWG = kThreads * kSeg;  // 2048 rows = 64 FRSZ2 blocks
 constexpr int kCounterBytes = 8192;  // ticket counters of the last-workgroup reductions
 constexpr int kMaxRestart = 512;  // largest restart length m
+constexpr double kDefaultEta = 0.7071067811865476;
+constexpr int kDefaultMaxIters = 20000;
 // Largest row count: row indices, row-group starts and the 8-row groups past
 // them (up to 2048 * row_groups(n)) all stay below 2^31 in 32-bit arithmetic.
 constexpr int64_t kMaxRows = (int64_t(1) << 31) - 4096;
@@ -41,6 +43,9 @@ constexpr int kBatchThreads = 512;
 constexpr int kBatchMaxN = 65536;
 constexpr int kBatchMaxRestart = 104;
 int64_t batch_workspace_bytes(int32_t n, int32_t m, int format);
+// The items (validated) by one workgroup each; a cb_status of the call, the
+// systems' own in results.
+int batch_without_teams(const cb_batch_item* items, int count, cb_result* results, hipStream_t s);
 
 // Serving ring (team_ring.hip): a persistent launch that takes small systems
 // from descriptors published while it runs, a team of workgroups each.
@@ -55,9 +60,10 @@ BatchRing* ring_create(int grid, int idle_polls, double slice_s);
 // CB_ERR_WORKSPACE if every slot is busy.
 int ring_publish(BatchRing* r, const cb_batch_item& q, const int32_t* h_row_ptr, const int32_t* h_col,
                  const double* h_val, const double* h_b, const double* h_x0, double* h_x, uint32_t* seq);
-// true once system seq has finished; then *res and *launch (the launch that
-// served it) are set and the handle is free again.
-bool ring_poll(BatchRing* r, uint32_t seq, cb_result* res, uint32_t* launch);
+// true once system seq has finished; then *res, *launch (the launch that served
+// it) and *solved are set and the handle is free again.  Not solved: its team did
+// not come together, and the system is as it was when it was published.
+bool ring_poll(BatchRing* r, uint32_t seq, cb_result* res, uint32_t* launch, bool* solved);
 // Launch the ring kernel on s unless a launch is still running or the CUs it
 // needs are reserved by other solves; returns the new launch's number, or 0 if
 // none was started.  CB status via *status.

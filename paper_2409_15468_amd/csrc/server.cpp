@@ -19,8 +19,10 @@
 //    then get their turn) or is idle while a lane's team waits for its CUs,
 //    and is started again while work is pending.
 // Which path a request takes depends on its own shape only, and neither
-// path's arithmetic depends on what runs beside it, so a result does not
-// depend on the mix it ran in.
+// path's arithmetic depends on the other requests, so a result does not depend on
+// the mix it ran in.  (Where the work of other programs on the GPU keeps a
+// team's workgroups from coming together, the request is solved without a team,
+// and its last bits are that path's.)
 #include <hip/hip_runtime.h>
 
 #include <atomic>
@@ -36,6 +38,7 @@
 #include <vector>
 
 #include "cb_internal.hpp"
+#include "team.hpp"
 
 namespace cb {
 
@@ -56,6 +59,7 @@ struct Request {
 struct cb_server {
     size_t budget;
     int device;
+    int32_t team_wait;  // of the thread that created the server (cb_internal_team_wait)
     std::chrono::steady_clock::time_point t0;
     std::mutex mu;
     std::condition_variable cv;
@@ -199,6 +203,7 @@ static bool has_kind(const cb_server* S, bool batch_lane) {
 
 static void worker_main(cb_server* S) {
     (void)hipSetDevice(S->device);
+    cb_internal_team_wait(S->team_wait, 0);
     hipStream_t s = nullptr;
     if (hipStreamCreateWithFlags(&s, hipStreamNonBlocking) != hipSuccess) return;
     const bool batch_lane = false;
@@ -301,15 +306,45 @@ static void fail_all_small(cb_server* S, int status) {
     S->ring_status = status;
 }
 
+// The systems whose teams did not come together, by one workgroup each, in the
+// device memory they have (requests' x: x0 before, the iterate after).
+static void solve_left(std::vector<InFlight>& left, unsigned char* dev, hipStream_t s) {
+    std::vector<cb_batch_item> items;
+    std::vector<cb_result> res(left.size());
+    int st = CB_OK;
+    for (InFlight& f : left) {
+        const Request& r = *f.r;
+        const Placed p = place(r, batch_workspace_bytes(r.n, r.m, r.format));
+        unsigned char* m = dev + f.doff;
+        if (!upload(r, m, p, s)) st = fail(CB_ERR_HIP, "input copy failed");
+        items.push_back(cb_batch_item{csr_at(r, m, p), reinterpret_cast<double*>(m + p.b),
+                                      reinterpret_cast<double*>(m + p.x), m + p.ws, (size_t)(p.total - p.ws), r.m,
+                                      r.format, r.tol});
+    }
+    if (st == CB_OK) st = batch_without_teams(items.data(), (int)items.size(), res.data(), s);
+    for (size_t i = 0; i < left.size(); ++i) {
+        Request& r = *left[i].r;
+        if (st == CB_OK &&
+            hipMemcpyAsync(r.x.data(), items[i].x, (size_t)r.n * 8, hipMemcpyDeviceToHost, s) != hipSuccess)
+            st = fail(CB_ERR_HIP, "result copy failed");
+        r.result = res[i];
+    }
+    if (hipStreamSynchronize(s) != hipSuccess && st == CB_OK) st = fail(CB_ERR_HIP, "solve failed");
+    for (InFlight& f : left)
+        if (st != CB_OK) f.r->result.status = st;
+}
+
 static void ring_main(cb_server* S) {
     (void)hipSetDevice(S->device);
-    hipStream_t ks = nullptr;
+    cb_internal_team_wait(S->team_wait, 0);
+    hipStream_t ks = nullptr, us = nullptr;  // the loop's launches, and what they leave unsolved
     BatchRing* ring = nullptr;
     unsigned char* dev = nullptr;
     unsigned char* stg = nullptr;
     unsigned char* stg_dev = nullptr;
     const int64_t arena_bytes = std::min<int64_t>((int64_t)S->budget, kRingArenaMax);
     if (hipStreamCreateWithFlags(&ks, hipStreamNonBlocking) != hipSuccess ||
+        hipStreamCreateWithFlags(&us, hipStreamNonBlocking) != hipSuccess ||
         !(ring = ring_create(kRingGrid, kRingIdlePolls, kRingSlice)) ||
         hipMalloc(reinterpret_cast<void**>(&dev), (size_t)arena_bytes) != hipSuccess ||
         hipHostMalloc(reinterpret_cast<void**>(&stg), (size_t)kStagingBytes,
@@ -325,11 +360,18 @@ static void ring_main(cb_server* S) {
     for (;;) {
         bool progressed = false;
         // finished systems: results back to their requests, memory to the budget
+        std::vector<InFlight> left;
         for (auto it = fl.begin(); it != fl.end();) {
             cb_result res;
             uint32_t launch = 0;
-            if (!ring_poll(ring, it->seq, &res, &launch)) {
+            bool solved = false;
+            if (!ring_poll(ring, it->seq, &res, &launch, &solved)) {
                 ++it;
+                continue;
+            }
+            if (!solved) {
+                left.push_back(*it);
+                it = fl.erase(it);
                 continue;
             }
             Request& r = *it->r;
@@ -344,6 +386,17 @@ static void ring_main(cb_server* S) {
             }
             S->cv.notify_all();
             it = fl.erase(it);
+            progressed = true;
+        }
+        if (!left.empty()) {
+            solve_left(left, dev, us);
+            for (InFlight& f : left) {
+                darena.release(f.doff, f.dbytes);
+                sarena.release(f.soff, f.st.total);
+                std::lock_guard<std::mutex> lk(S->mu);
+                finish(S, *f.r, S->now());
+            }
+            S->cv.notify_all();
             progressed = true;
         }
         // admission by budget, in arrival order
@@ -459,6 +512,7 @@ static void ring_main(cb_server* S) {
     if (dev) (void)hipFree(dev);
     if (stg) (void)hipHostFree(stg);
     if (ks) (void)hipStreamDestroy(ks);
+    if (us) (void)hipStreamDestroy(us);
 }
 
 }  // namespace cb
@@ -485,6 +539,7 @@ cb_server* cb_server_create(size_t hbm_budget_bytes, int device, int lanes) {
     cb_server* S = new cb_server();
     S->budget = hbm_budget_bytes;
     S->device = device;
+    S->team_wait = team_wait_setting();
     S->t0 = std::chrono::steady_clock::now();
     for (int i = 0; i < lanes; ++i) S->workers.emplace_back(worker_main, S);
     S->workers.emplace_back(ring_main, S);

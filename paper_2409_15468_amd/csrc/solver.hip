@@ -408,8 +408,8 @@ static int solve_impl(const cb_csr& A, const double* b, double* x, int m, double
                       const double* dinv = nullptr, const double* pval = nullptr, bool plan_ready = false) {
     const double t0 = now_s();
     const int n = A.n;
-    const double eta = (opt && opt->eta > 0) ? opt->eta : 0.7071067811865476;
-    const int max_iters = (opt && opt->max_iters > 0) ? opt->max_iters : 20000;
+    const double eta = (opt && opt->eta > 0) ? opt->eta : kDefaultEta;
+    const int max_iters = (opt && opt->max_iters > 0) ? opt->max_iters : kDefaultMaxIters;
     const int max_cycles = opt ? opt->max_cycles : 0;
     const int literal = opt ? opt->literal_breakdown : 0;
     const int fuse_opt = opt ? opt->fuse_updates : 0;

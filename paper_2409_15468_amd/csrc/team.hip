@@ -110,6 +110,7 @@ int64_t team_ll_words(int G, int m) {
 }
 
 static thread_local int32_t g_wait_us = -1, g_wait_skip = 0;
+int32_t team_wait_setting() { return g_wait_us; }
 int32_t team_wait_us() {
     if (g_wait_us < 0 || g_wait_skip-- > 0) return kTeamWaitUs;
     return g_wait_us;

@@ -37,6 +37,8 @@ struct TeamArgs {
     double* w;           // n doubles: the vector the next SpMV reads
     uint64_t* ll;        // exchange slots
     unsigned* join;      // workgroups that have come; top bit: the team does not form
+    unsigned* busy;      // NULL, or the teams of this launch that are whole: while there are any, others
+                         // wait for their workgroups
     double* x0;          // NULL, or n doubles that get x as it was on entry
     State* st;
     double* hist;        // NULL, or |g_{j+1}| per step of this launch
@@ -68,6 +70,7 @@ inline void team_exchange(TeamArgs& a, uint64_t* p) {
 // kTeamWaitUs, or what cb_internal_team_wait has set for the next launch of this
 // host thread.
 int32_t team_wait_us();
+int32_t team_wait_setting();
 // Clear the words at a.join and start the team on stream s.
 void launch_team(int fmt, const TeamArgs& a, hipStream_t s);
 // The team for one of many systems; depends on its rows only.
@@ -100,3 +103,5 @@ private:
 };
 
 }  // namespace cb
+
+extern "C" void cb_internal_team_wait(int32_t us, int32_t launches);

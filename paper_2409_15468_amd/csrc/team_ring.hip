@@ -2,7 +2,8 @@
 // descriptors the host publishes while it runs (continuous batching), each
 // solved by a team of workgroups (team_solve.hpp) of the shape the batched
 // solver gives it, so that a request's result is the batched solver's, bit for
-// bit.  (With one workgroup a request, a system of 16384 rows took 190 ms;
+// bit; if other programs' work keeps a team from forming, the host solves the
+// system like the batch does then.  (With one workgroup a request, a system of 16384 rows took 190 ms;
 // with a team of 16, 16 ms.)
 //
 // A published system is G units, one per workgroup of its team, consecutive in
@@ -52,7 +53,6 @@ using namespace dev;
 namespace {
 
 constexpr int kRingUnits = 1 << 16;  // units published and unclaimed at most (a power of two)
-constexpr int32_t kRingWaitUs = 20000000;  // a team may wait for workgroups that finish other systems
 
 struct RingDesc {
     TeamArgs a;
@@ -199,8 +199,9 @@ struct BatchRing {
     RingCtl* ctl_dev = nullptr;
     RingDesc* descs_dev = nullptr;
     State* results_dev = nullptr;
-    unsigned char* mem = nullptr;   // device: claim counter, arrivals per slot, exchange words per slot
+    unsigned char* mem = nullptr;   // device: claim counter, whole teams, arrivals per slot, exchange words per slot
     uint64_t* head = nullptr;
+    unsigned* busy = nullptr;
     unsigned* arrived = nullptr;
     uint64_t* ll = nullptr;
     int64_t ll_words = 0;           // per slot
@@ -250,6 +251,7 @@ BatchRing* ring_create(int grid, int idle_polls, double slice_s) {
         return nullptr;
     }
     r->head = reinterpret_cast<uint64_t*>(r->mem);
+    r->busy = reinterpret_cast<unsigned*>(r->mem + 128);
     r->arrived = reinterpret_cast<unsigned*>(r->mem + 256);
     r->ll = reinterpret_cast<uint64_t*>(r->mem) + 32 + kRingSlots / 2;
     unsigned char* d = static_cast<unsigned char*>(dptr);
@@ -280,11 +282,12 @@ int ring_publish(BatchRing* r, const cb_batch_item& q, const int32_t* h_row_ptr,
     }
     RingDesc d{};
     d.a = team_batch_args(q);
-    d.a.eta = 0.7071067811865476;
-    d.a.max_iters = 20000;
+    d.a.eta = kDefaultEta;
+    d.a.max_iters = kDefaultMaxIters;
     team_exchange(d.a, ll);
     d.a.st = r->results_dev + slot;
-    d.a.wait_us = team_wait_us() == 0 ? 0 : kRingWaitUs;
+    d.a.wait_us = team_wait_us();
+    d.a.busy = r->busy;
     d.a.epoch0 = r->epoch[slot];
     d.h_row_ptr = h_row_ptr;
     d.h_col = h_col;
@@ -307,14 +310,12 @@ int ring_publish(BatchRing* r, const cb_batch_item& q, const int32_t* h_row_ptr,
     return CB_OK;
 }
 
-bool ring_poll(BatchRing* r, uint32_t seq, cb_result* res, uint32_t* launch) {
+bool ring_poll(BatchRing* r, uint32_t seq, cb_result* res, uint32_t* launch, bool* solved) {
     const int slot = (int)seq;
     if (__atomic_load_n(&r->ctl->done[slot], __ATOMIC_ACQUIRE) != r->seq_of[slot] + 1u) return false;
     const State& st = r->results[slot];
-    if (res) {
-        fill_result(res, st, 0.0);
-        if (st.status == kTeamAbandoned || st.status == kTeamLost) res->status = CB_ERR_HIP;
-    }
+    *solved = st.status != kTeamAbandoned && st.status != kTeamLost;
+    if (res) fill_result(res, st, 0.0);
     // (a lost team may have used tags past those its first workgroup reports, one
     // that never formed has used none)
     if (st.status == kTeamLost) r->epoch[slot] = UINT32_MAX;

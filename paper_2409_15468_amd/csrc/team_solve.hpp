@@ -144,7 +144,9 @@ __device__ __forceinline__ bool ll_load(const Ctx& x, const uint64_t* const* s, 
 }
 
 // True once all G workgroups of the team are on the GPU; false, in every one of
-// them, if they are not within wait_us (all threads).  The count and the
+// them, if they are not within wait_us (all threads).  Where a launch's
+// workgroups go on to other systems, the time counts while none of its teams is
+// whole: then every workgroup of it that the GPU has is in this one.    The count and the
 // decision against the team share a word: a workgroup gives up by setting the top
 // bit of a count that is not full, and a count with that bit is never full.
 __device__ __forceinline__ bool gather(Ctx& x) {
@@ -153,9 +155,13 @@ __device__ __forceinline__ bool gather(Ctx& x) {
         const int us = x.arg(&TeamArgs::wait_us);
         if (us <= 0) __hip_atomic_fetch_or(join, kNoTeam, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         unsigned v = __hip_atomic_fetch_add(join, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
-        const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
+        unsigned* busy = x.arg(&TeamArgs::busy);
+        uint64_t t0 = __builtin_amdgcn_s_memrealtime();
         while (v != (unsigned)x.G && !(v & kNoTeam)) {
-            if (__builtin_amdgcn_s_memrealtime() - t0 > (uint64_t)us * 100u) {
+            const uint64_t now = __builtin_amdgcn_s_memrealtime();
+            if (busy && ld_ctl(busy) != 0u) {
+                t0 = now;
+            } else if (now - t0 > (uint64_t)us * 100u) {
                 if (__hip_atomic_compare_exchange_strong(join, &v, v | kNoTeam, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                          __HIP_MEMORY_SCOPE_AGENT))
                     v |= kNoTeam;
@@ -165,6 +171,8 @@ __device__ __forceinline__ bool gather(Ctx& x) {
             v = ld_ctl(join);
         }
         x.S.dead = v & kNoTeam ? 1 : 0;
+        if (busy && x.rank == 0 && !(v & kNoTeam))
+            __hip_atomic_fetch_add(busy, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
     return uniform(x.S.dead) == 0;
@@ -807,6 +815,8 @@ __device__ __forceinline__ void team_solve(int rank, TeamShared& S) {
     }
     if (rank != 0) return;
     if (tid == 0) {
+        if (unsigned* busy = x.arg(&TeamArgs::busy))
+            __hip_atomic_fetch_sub(busy, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         S.st.nb = nb;
         if (status != kTeamLost) {
             S.st.iters = iters;

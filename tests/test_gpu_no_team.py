@@ -3,6 +3,8 @@ programs' work holds the CUs; here the wait for it is set to 0, so the
 launch leaves at once): the launch-per-kernel solver and the one-workgroup
 batch kernel take them from the x the caller gave, and do everything that the
 solver's and the batch's own tests ask for."""
+import time
+
 import numpy as np
 import pytest
 
@@ -10,6 +12,7 @@ import oracle
 import paper_2409_15468_amd as cb
 import synth
 from tests import test_gpu_batch as batch
+from tests import test_gpu_server as server
 from tests import test_gpu_solve as solve
 
 torch = pytest.importorskip("torch")
@@ -120,3 +123,24 @@ def test_batch_ragged(fmt, n, m):
 def test_batch_edges():
     batch.test_edge_cases()
     batch.test_literal_breakdown_option()
+
+
+def test_served_requests():
+    server.test_alone_equals_mixed_and_meets_tolerance()
+
+
+def test_served_result_is_the_batch_s():
+    """The served x is, bit for bit, that of a batch without teams."""
+    A = synth.convection_diffusion(45, 2, (20.0, 0.0))
+    b = synth.rhs_from_solution(A, np.random.default_rng(8).uniform(-1, 1, A.n))
+    x0 = np.random.default_rng(9).uniform(-1, 1, A.n)
+    res, xs, _ = batch.batch([(A, b, 30, 1e-9, "frsz2_21", x0)])
+    srv = cb.Server(1 << 30, 0, lanes=1)
+    t = srv.submit(A.row_ptr, A.col, A.val, b, 30, 1e-9, "frsz2_21", x0=x0)
+    got, t0 = None, time.time()
+    while got is None and time.time() - t0 < 20:
+        time.sleep(0.001)
+        got = srv.poll(t, A.n)
+    srv.close()
+    assert got is not None and np.array_equal(got[0], xs[0])
+    assert got[1]["status"] == 0 and got[1]["iterations"] == res[0]["iterations"]
