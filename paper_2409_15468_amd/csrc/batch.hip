@@ -461,8 +461,7 @@ BatchItem item_of(const cb_batch_item& q) {
                      q.A.n, q.A.nnz, q.m, q.format, q.tol};
 }
 
-// The systems by teams of workgroups, in as few launches as fit the GPU: the
-// longest systems first, so that the systems of a launch take about as long.
+// The systems by teams of workgroups in one launch, the longest systems first.
 // Appends to `left` those that have to take the other path.
 int solve_by_teams(const cb_batch_item* items, int count, const BatchOpts& o, cb_result* results_host,
                    std::vector<int>& left, hipStream_t s) {
@@ -486,53 +485,37 @@ int solve_by_teams(const cb_batch_item* items, int count, const BatchOpts& o, cb
     }
     if (order.empty()) return CB_OK;
     std::stable_sort(order.begin(), order.end(), [&](int p, int q) { return args[p].n > args[q].n; });
-    // launches: systems in order, each into the first launch that has room
-    std::vector<int> room, launch_of(count, -1);
-    for (int i : order) {
-        size_t l = 0;
-        while (l < room.size() && room[l] < args[i].G) ++l;
-        if (l == room.size()) room.push_back(cap);
-        room[l] -= args[i].G;
-        launch_of[i] = (int)l;
-    }
-    std::vector<uint64_t> map;
-    std::vector<size_t> first;
-    for (size_t l = 0; l < room.size(); ++l) {
-        first.push_back(map.size());
-        for (int i : order)
-            if (launch_of[i] == (int)l)
-                for (int g = 0; g < args[i].G; ++g) map.push_back((uint64_t)g << 32 | (uint32_t)i);
-    }
-    first.push_back(map.size());
-    // device block: arguments, the map, results, exchange slots
-    const int64_t o_map = al256((int64_t)count * sizeof(TeamArgs)), o_st = o_map + al256((int64_t)map.size() * 8);
-    const int64_t o_ll = o_st + al256((int64_t)count * sizeof(State)), total = o_ll + 8 * ll_words;
+    std::vector<uint64_t> units;
+    for (int i : order)
+        for (int g = 0; g < args[i].G; ++g) units.push_back((uint64_t)g << 32 | (uint32_t)i);
+    const int grid = (int)std::min<size_t>(units.size(), (size_t)cap);
+    // device block: arguments, the units, results; the ticket and the count of
+    // whole teams in a line each, and the exchange words
+    const int64_t o_units = al256((int64_t)count * sizeof(TeamArgs)), o_st = o_units + al256((int64_t)units.size() * 8);
+    const int64_t o_next = o_st + al256((int64_t)count * sizeof(State)), o_ll = o_next + 256, total = o_ll + 8 * ll_words;
     unsigned char* mem = nullptr;
     CB_HIP(hipMallocAsync(reinterpret_cast<void**>(&mem), (size_t)total, s));
     int64_t at = 0;
     for (int i : order) {
         team_exchange(args[i], reinterpret_cast<uint64_t*>(mem + o_ll) + at);
         args[i].st = reinterpret_cast<State*>(mem + o_st) + i;
+        args[i].busy = reinterpret_cast<unsigned*>(mem + o_next + 128);
         at += team_ll_words(args[i].G, args[i].m);
     }
     std::vector<unsigned char> host((size_t)o_st, 0);
     std::memcpy(host.data(), args.data(), (size_t)count * sizeof(TeamArgs));
-    std::memcpy(host.data() + o_map, map.data(), map.size() * 8);
+    std::memcpy(host.data() + o_units, units.data(), units.size() * 8);
     std::vector<State> states(count);
     int st = CB_OK;
     {
-        size_t most = 0;
-        for (size_t l = 0; l < room.size(); ++l) most = std::max(most, first[l + 1] - first[l]);
-        TeamSeats seats((int)most, cap);
+        TeamSeats seats(grid, cap);
         seats.wait();
         if (hipMemcpyAsync(mem, host.data(), host.size(), hipMemcpyHostToDevice, s) != hipSuccess) {
             st = fail(CB_ERR_HIP, "descriptor copy failed");
         } else {
-            launch_team_clear(reinterpret_cast<uint64_t*>(mem + o_ll), ll_words, s);
-            for (size_t l = 0; l < room.size(); ++l)
-                launch_team_many(reinterpret_cast<const TeamArgs*>(mem),
-                                 reinterpret_cast<const uint64_t*>(mem + o_map) + first[l],
-                                 (int)(first[l + 1] - first[l]), s);
+            launch_team_clear(reinterpret_cast<uint64_t*>(mem + o_next), ll_words + 32, s);
+            launch_team_many(reinterpret_cast<const TeamArgs*>(mem), reinterpret_cast<const uint64_t*>(mem + o_units),
+                             (unsigned)units.size(), reinterpret_cast<unsigned*>(mem + o_next), grid, s);
             if (hipGetLastError() != hipSuccess ||
                 hipMemcpyAsync(states.data(), mem + o_st, (size_t)count * sizeof(State), hipMemcpyDeviceToHost, s) !=
                     hipSuccess)

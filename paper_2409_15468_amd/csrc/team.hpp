@@ -78,9 +78,11 @@ TeamShape team_batch_shape(int32_t n);
 // Its arguments but for ll, st, eta, max_iters and literal.
 TeamArgs team_batch_args(const cb_batch_item& q);
 void launch_team_clear(uint64_t* ll, int64_t words, hipStream_t s);
-// One launch of `groups` workgroups: workgroup w is workgroup map[w] >> 32 of
-// the team of system (uint32_t)map[w] (args and map on the device, slots clear).
-void launch_team_many(const TeamArgs* args, const uint64_t* map, int groups, hipStream_t s);
+// One launch of `groups` workgroups, at least the largest team, that take the
+// `count` units in order (args and units on the device; *next, the busy word and
+// the exchange words clear).
+void launch_team_many(const TeamArgs* args, const uint64_t* units, unsigned count, unsigned* next, int groups,
+                      hipStream_t s);
 
 // The statistics of a solve as the caller gets them.
 void fill_result(cb_result* res, const State& hs, double seconds);

@@ -115,6 +115,37 @@ def test_batch_over_several_launches():
         assert np.array_equal(alone[2].cpu().numpy(), x), sizes[i]
 
 
+def test_batch_does_not_wait_for_its_slow_systems_in_turn():
+    """1280 one-workgroup systems, five times what the GPU holds, of which every
+    256th runs 2000 steps (a tolerance it cannot meet): the slow ones run side by
+    side.  One after the other they would take five times what they take alone;
+    less than half of that is asked for."""
+    A = synth.convection_diffusion(20, 2, (20.0, 0.0))
+    b = torch.from_numpy(synth.rhs_from_solution(A, np.random.default_rng(1).uniform(-1, 1, A.n))).cuda()
+    Ad = cb.DeviceCSR.from_host(A.row_ptr, A.col, A.val)
+
+    def run(tols):
+        x = torch.zeros((len(tols), A.n), dtype=torch.float64, device="cuda")
+        size = cb.cbgmres_batch_workspace_bytes(A.n, 30, "frsz2_32")
+        ws = [torch.empty(size, dtype=torch.uint8, device="cuda") for _ in tols]
+        best = 1e9
+        for _ in range(3):
+            x.zero_()
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            res = cb.cbgmres_solve_batch([(Ad, b, xi, 30, tol, "frsz2_32") for xi, tol in zip(x, tols)], workspaces=ws,
+                                         max_iters=2000)
+            best = min(best, time.perf_counter() - t)
+        return best, res, x
+
+    slow, _, _ = run([1e-30] * 5)
+    mixed, res, x = run([1e-30 if i % 256 == 7 else 1e-6 for i in range(1280)])
+    print(f"slow ones alone {slow * 1e3:.1f} ms, mixed {mixed * 1e3:.1f} ms", flush=True)
+    assert mixed < 2.5 * slow
+    assert all(r["iterations"] == 2000 if i % 256 == 7 else r["converged"] for i, r in enumerate(res))
+    assert torch.equal(x[0].expand(1280, -1)[:7], x[:7]) and torch.equal(x[0], x[1279])
+
+
 def test_served_small_then_large():
     """A small request starts the serving launch (128 workgroups); the larger
     ones after it need 138 and 256 of the GPU's CUs, so they run only if
