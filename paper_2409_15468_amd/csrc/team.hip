@@ -27,8 +27,8 @@ __global__ void k_team_clear(uint64_t* __restrict__ ll, int64_t words) {
 }
 
 // The CUs that team workgroups of this process occupy, per device, in arrival
-// order: a solve waits until its whole team fits, so two teams never hold
-// parts of the GPU that the other needs to become whole.
+// order: a solve waits until its whole team fits, so two teams never hold parts of
+// the GPU that the other needs to become whole (seats_of).
 constexpr int kLedgerDevices = 16;
 struct Ledger {
     std::mutex mu;
@@ -48,7 +48,14 @@ int team_device_groups() {
     return cus < kTeamMaxGroups ? cus : kTeamMaxGroups;
 }
 
-TeamSeats::TeamSeats(int groups, int capacity) : groups_(groups), capacity_(capacity) {
+// Workgroup w of a launch runs on XCD w % kXcds whatever else runs there, so a
+// team of 9 takes two CUs of the first: seats are counted in rows of one per XCD.
+static int seats_of(int groups, int capacity) {
+    const int rows = (groups + kXcds - 1) / kXcds;
+    return rows * kXcds < capacity ? rows * kXcds : capacity;
+}
+
+TeamSeats::TeamSeats(int groups, int capacity) : groups_(seats_of(groups, capacity)), capacity_(capacity) {
     if (hipGetDevice(&dev_) != hipSuccess || dev_ < 0 || dev_ >= kLedgerDevices) dev_ = 0;
     std::lock_guard<std::mutex> lk(g_ledger[dev_].mu);
     ticket_ = g_ledger[dev_].next++;
@@ -143,6 +150,9 @@ void launch_team(int fmt, const TeamArgs& a, hipStream_t s) {
 }
 
 }  // namespace cb
+
+// (for tests)
+extern "C" int32_t cb_internal_team_seats(int32_t groups, int32_t capacity) { return cb::seats_of(groups, capacity); }
 
 // How long the teams of this host thread's solves wait for their workgroups, in
 // microseconds (negative: the default), from the launch after the next
