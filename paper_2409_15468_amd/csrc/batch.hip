@@ -465,7 +465,7 @@ BatchItem item_of(const cb_batch_item& q) {
 // Appends to `left` those that have to take the other path.
 int solve_by_teams(const cb_batch_item* items, int count, const BatchOpts& o, cb_result* results_host,
                    std::vector<int>& left, hipStream_t s) {
-    const int cap = team_device_groups();
+    const int cap = team_stream_groups(s);
     std::vector<TeamArgs> args(count);
     std::vector<int> order;
     int64_t ll_words = 0;

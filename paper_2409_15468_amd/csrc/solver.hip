@@ -340,7 +340,7 @@ void fill_result(cb_result* res, const State& hs, double seconds) {
 static int solve_team(const cb_csr& A, const double* b, double* x, int m, int fmt, const Ws& W, const TeamArgs& opts,
                       const double* dinv, const double* pval, double* history_host, int64_t history_cap,
                       cb_result* res, double t0, Carry* done, hipStream_t s) {
-    const int n = A.n, cap = team_device_groups();
+    const int n = A.n, cap = team_stream_groups(s);
     TeamShape sh;
     if (spmv_lanes_per_row(n, A.nnz) != 0 || !team_shape(n, m, cap, &sh)) return kTeamAbandoned;
     const int64_t ll_bytes = 8 * team_ll_words(sh.G, m);

@@ -48,6 +48,22 @@ int team_device_groups() {
     return cus < kTeamMaxGroups ? cus : kTeamMaxGroups;
 }
 
+int team_stream_groups(hipStream_t s) {
+    const int cap = team_device_groups();
+    int dev = 0, cus = 0;
+    uint32_t mask[32] = {};
+    if (!s || s == hipStreamPerThread || cap == 0 || hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        return cap;
+    if (hipExtStreamGetCUMask(s, 32, mask) != hipSuccess) {
+        (void)hipGetLastError();
+        return cap;
+    }
+    int enabled = 0;
+    for (uint32_t w : mask) enabled += __builtin_popcount(w);
+    return enabled < cus ? 0 : cap;
+}
+
 // Workgroup w of a launch runs on XCD w % kXcds whatever else runs there, so a
 // team of 9 takes two CUs of the first: seats are counted in rows of one per XCD.
 static int seats_of(int groups, int capacity) {

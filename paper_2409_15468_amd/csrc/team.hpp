@@ -59,6 +59,9 @@ struct TeamShape {
 
 // Workgroups a team may have on the current device (0: no teams).
 int team_device_groups();
+// ... for work on stream s: 0 if it may not use all CUs (a CU mask), since a team
+// needs the CUs it counts on.
+int team_stream_groups(hipStream_t s);
 // The team for n rows and restart length m; false if it does not fit.
 bool team_shape(int32_t n, int32_t m, int capacity, TeamShape* s);
 int64_t team_ll_words(int G, int m);

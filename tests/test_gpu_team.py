@@ -9,6 +9,7 @@ The matrix has a diagonal of 4 and off-diagonals whose absolute sum is at most
 of at most 1e-10 differ by at most 2 kappa 1e-10 = 6e-10 there, and by at most
 that times sqrt(n) / 1 in the 2-norm relative to ||x|| for entries of like
 size; 1e-8 is asked for."""
+import ctypes as C
 import time
 
 import numpy as np
@@ -144,6 +145,68 @@ def test_batch_does_not_wait_for_its_slow_systems_in_turn():
     assert mixed < 2.5 * slow
     assert all(r["iterations"] == 2000 if i % 256 == 7 else r["converged"] for i, r in enumerate(res))
     assert torch.equal(x[0].expand(1280, -1)[:7], x[:7]) and torch.equal(x[0], x[1279])
+
+
+def test_every_ordinary_stream_has_teams():
+    """The same bits on the default stream and on another one, and other bits
+    than where no team forms."""
+    A = near_diagonal(20000, 3)
+    b = torch.from_numpy(A.scipy() @ np.random.default_rng(7).uniform(-1, 1, A.n)).cuda()
+    Ad = cb.DeviceCSR.from_host(A.row_ptr, A.col, A.val)
+
+    def run():
+        x = torch.zeros(A.n, dtype=torch.float64, device="cuda")
+        torch.cuda.synchronize()
+        assert cb.cbgmres_solve(Ad, b, x, 30, 1e-10, "float32")[0]["converged"]
+        torch.cuda.synchronize()
+        return x
+
+    first = run()
+    with torch.cuda.stream(torch.cuda.Stream()):
+        assert torch.equal(run(), first)
+    cb.lib().cb_internal_team_wait(0, 0)
+    try:
+        assert not torch.equal(run(), first)
+    finally:
+        cb.lib().cb_internal_team_wait(-1, 0)
+
+
+def test_stream_that_may_use_half_the_cus():
+    """On a stream with a CU mask no team is tried: the solve and the batch take
+    their other paths at once (within half the time that a team is waited for)."""
+    hip = cb.lib()  # (its HIP runtime)
+    torch.zeros(1, device="cuda")
+    words = -(-torch.cuda.get_device_properties(0).multi_processor_count // 32)
+    mask = (C.c_uint32 * words)(*[0x55555555] * words)
+    h = C.c_void_p()
+    if hip.hipExtStreamCreateWithCUMask(C.byref(h), words, mask) != 0:
+        pytest.skip("the driver here makes no streams with a CU mask")
+    A = near_diagonal(131072, 4)
+    b = A.scipy() @ np.random.default_rng(5).uniform(-1, 1, A.n)
+    small = near_diagonal(3000, 4)
+    bs = small.scipy() @ np.random.default_rng(6).uniform(-1, 1, small.n)
+    stream = torch.cuda.ExternalStream(h.value)
+    try:
+        with torch.cuda.stream(stream):
+            Ad, As = (cb.DeviceCSR.from_host(M.row_ptr, M.col, M.val) for M in (A, small))
+            bd, bsd = torch.from_numpy(b).cuda(), torch.from_numpy(bs).cuda()
+            for _ in range(2):
+                x, xs = (torch.zeros(M.n, dtype=torch.float64, device="cuda") for M in (A, small))
+                stream.synchronize()
+                t = time.perf_counter()
+                res, _ = cb.cbgmres_solve(Ad, bd, x, 30, 1e-10, "frsz2_32")
+                t1 = time.perf_counter()
+                rb = cb.cbgmres_solve_batch([(As, bsd, xs, 30, 1e-10, "frsz2_32")])[0]
+                t2 = time.perf_counter()
+                print(f"solve {t1 - t:.4f} s, batch {t2 - t1:.4f} s", flush=True)
+            assert t1 - t < 0.05 and t2 - t1 < 0.05
+            for M, rhs, sol, r in ((A, b, x, res), (small, bs, xs, rb)):
+                assert r["converged"]
+                assert np.linalg.norm(rhs - M.scipy() @ sol.cpu().numpy()) <= 1e-10 * (1 + 1e-6) * np.linalg.norm(rhs)
+            stream.synchronize()
+    finally:
+        torch.cuda.synchronize()
+        assert hip.hipStreamDestroy(h) == 0
 
 
 def test_served_small_then_large():
