@@ -261,7 +261,11 @@ typedef struct cb_options {
                                   does not ask for it): 0 (default) per cycle, when the
                                   last cycle re-orthogonalised at least half its steps
                                   (never for a float64 basis); 1 never; 2 always.  The
-                                  arithmetic is the same either way. */
+                                  arithmetic is the same either way.  1 and 2 run the
+                                  solve as one launch per operation; with 0, systems of
+                                  up to 8 entries a row, about half a million rows and
+                                  m <= 104 run as one launch of resident workgroups,
+                                  which sums in another order. */
 } cb_options;
 
 typedef struct cb_result {
@@ -274,7 +278,8 @@ typedef struct cb_result {
     double rel_residual;         /* last explicit ||b - A x|| / ||b||; -1 if not evaluated */
     double implicit_rel_residual;/* last |g_{j+1}| / ||b|| */
     double seconds;              /* wall time of the solve */
-    double basis_bytes;          /* algorithmic bytes read+written in the basis kernels */
+    double basis_bytes;          /* algorithmic bytes read+written in the basis kernels (the same
+                                    count however the solve is launched) */
 } cb_result;
 
 /* Device workspace bytes cbgmres_solve needs for n rows, restart m, format. */

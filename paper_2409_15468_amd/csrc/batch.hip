@@ -572,6 +572,7 @@ TeamArgs team_batch_args(const cb_batch_item& q) {
     a.cs = sh.cs;
     a.hist_cap = INT32_MAX - 2 * kTeamMaxRestart;
     a.format = q.format;
+    a.batch = 1;
     return a;
 }
 

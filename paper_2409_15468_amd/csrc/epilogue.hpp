@@ -46,7 +46,9 @@ struct State {
     int32_t prev_steps;
     int32_t iters, reorths, breakdowns, converged;
     int32_t stop, status, cycles, max_iters;
-    int32_t literal, pad0, pad1, pad2;
+    int32_t literal, pad0;
+    int32_t counted_fused;  // a team's next cycle counts as one of fused updates (basis_bytes)
+    int32_t pad2;
 };
 
 enum EpiMode : int {

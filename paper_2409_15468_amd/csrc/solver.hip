@@ -415,7 +415,7 @@ static int solve_impl(const cb_csr& A, const double* b, double* x, int m, double
     const int fuse_opt = opt ? opt->fuse_updates : 0;
 
     Carry from{};
-    {
+    if (fuse_opt != 1 && fuse_opt != 2) {  // (they ask for the launches below)
         TeamArgs o{};
         o.tol = tol;
         o.eta = eta;

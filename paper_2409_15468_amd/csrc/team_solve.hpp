@@ -80,6 +80,7 @@ struct TeamShared {
     State st;      // what the solve reports, kept by thread 0
     double carry;  // column j's entry after the old rotations
     int bad, dead;
+    int reorths0;  // S.st.reorths at the start of the cycle
 };
 static_assert(sizeof(TeamShared) <= 148 * 1024, "team LDS (and 10.5 KB of frsz2_21 tiles)");
 
@@ -520,12 +521,17 @@ __device__ __forceinline__ void team_solve(int rank, TeamShared& S) {
             S.st.breakdowns = ld_ctl(&st->breakdowns);
             S.st.basis_bytes = ld_ctl(&st->basis_bytes);
             S.st.gabs = ld_ctl(&st->gabs);
+            S.st.counted_fused = ld_ctl(&st->counted_fused);
         }
     } else if (tid == 0) {
         S.st = State{};
         S.st.gabs = -1.0;
+        S.st.counted_fused = FMT != CB_F64 && !x.arg(&TeamArgs::batch);
     }
-    if (tid == 0) S.st.rel = -1.0;
+    if (tid == 0) {
+        S.st.rel = -1.0;
+        S.reorths0 = S.st.reorths;
+    }
     // One loop, so that each piece of code exists once: the phase of an
     // iteration is ||b||, the residual of a restart, an Arnoldi step (j) or the
     // update of x; each ends in an exchange of a squared norm.
@@ -788,9 +794,19 @@ __device__ __forceinline__ void team_solve(int rank, TeamShared& S) {
                 over = gabs <= x.arg(&TeamArgs::tol) * nb || bd || iters >= x.arg(&TeamArgs::max_iters) || jc == x.m;
             }
             if (tid == 0) {
-                S.st.basis_bytes += (again ? 4.0 : 3.0) * jc * (double)x.arg(&TeamArgs::V).col_bytes;
+                // the passes over the columns as the other paths make them: fused
+                // updates form u whether or not it is asked for, separate ones
+                // (a float64 basis, the batch, cycles that follow one with few
+                // second passes) only if it is
+                const int passes = S.st.counted_fused ? 3 + again : 2 + 2 * again;
+                S.st.basis_bytes += (double)passes * jc * (double)x.arg(&TeamArgs::V).col_bytes;
                 S.st.reorths += again;
-                if (over) S.st.breakdowns += bd;
+                if (over) {
+                    S.st.breakdowns += bd;
+                    if (FMT != CB_F64 && !x.arg(&TeamArgs::batch))
+                        S.st.counted_fused = steps > 0 && 2 * (S.st.reorths - S.reorths0) >= steps;
+                    S.reorths0 = S.st.reorths;
+                }
             }
             if (over) {
                 recorded += steps;

@@ -147,6 +147,60 @@ def test_batch_does_not_wait_for_its_slow_systems_in_turn():
     assert torch.equal(x[0].expand(1280, -1)[:7], x[:7]) and torch.equal(x[0], x[1279])
 
 
+@pytest.mark.parametrize("fmt", ["float64", "frsz2_32"])
+@pytest.mark.parametrize("eta", [None, 0.2])
+def test_basis_bytes_are_those_of_the_other_paths(fmt, eta):
+    """The count of passes over the columns does not depend on how a solve is
+    launched: a team, or one launch per operation (m = 3 with a history: several
+    launches of a team); with eta = 0.2 few steps ask for the second pass, so a
+    cycle of fused updates is followed by separate ones."""
+    kw = {} if eta is None else {"eta": eta}
+    A = synth.convection_diffusion(40, 2, (20.0, 0.0))
+    b = torch.from_numpy(synth.rhs_from_solution(A, np.random.default_rng(2).uniform(-1, 1, A.n))).cuda()
+    Ad = cb.DeviceCSR.from_host(A.row_ptr, A.col, A.val)
+
+    def run(m, iters, wait, batch=False):
+        cb.lib().cb_internal_team_wait(wait, 0)
+        try:
+            x = torch.zeros(A.n, dtype=torch.float64, device="cuda")
+            if batch:
+                return cb.cbgmres_solve_batch([(Ad, b, x, m, 1e-14, fmt)], max_iters=iters, **kw)[0]
+            return cb.cbgmres_solve(Ad, b, x, m, 1e-14, fmt, max_iters=iters, history_cap=100, **kw)[0]
+        finally:
+            cb.lib().cb_internal_team_wait(-1, 0)
+
+    for m, iters in ((3, 40), (25, 70)):
+        for batch in (False, True):
+            team, other = run(m, iters, -1, batch), run(m, iters, 0, batch)
+            print(fmt, eta, m, batch, team["reorths"], team["basis_bytes"], flush=True)
+            assert team["iterations"] == other["iterations"] == iters
+            assert team["reorths"] == other["reorths"] and team["basis_bytes"] == other["basis_bytes"]
+
+
+@pytest.mark.parametrize("fuse", [1, 2])
+def test_fuse_updates_asks_for_the_launches(fuse):
+    """fuse_updates 1 and 2: bit for bit the solve without teams, and by their
+    own count of passes (separate: 2 + 2 per second pass, fused: 3 + 1)."""
+    A = synth.convection_diffusion(40, 2, (20.0, 0.0))
+    b = torch.from_numpy(synth.rhs_from_solution(A, np.random.default_rng(2).uniform(-1, 1, A.n))).cuda()
+    Ad = cb.DeviceCSR.from_host(A.row_ptr, A.col, A.val)
+    got = []
+    for wait in (-1, 0):
+        cb.lib().cb_internal_team_wait(wait, 0)
+        try:
+            x = torch.zeros(A.n, dtype=torch.float64, device="cuda")
+            got.append((cb.cbgmres_solve(Ad, b, x, 30, 1e-14, "float64", max_iters=30, fuse_updates=fuse, eta=0.2)[0], x))
+        finally:
+            cb.lib().cb_internal_team_wait(-1, 0)
+    (r, x), (r0, x0) = got
+    assert torch.equal(x, x0) and r["basis_bytes"] == r0["basis_bytes"]
+    assert r["reorths"] < 30
+    columns = sum(range(1, 31))
+    least = (3 if fuse == 2 else 2) * columns + 30
+    passes = r["basis_bytes"] / (cb.cb_basis_column_bytes("float64", A.n))
+    assert passes == least if r["reorths"] == 0 else least < passes < 4 * columns + 30
+
+
 def test_every_ordinary_stream_has_teams():
     """The same bits on the default stream and on another one, and other bits
     than where no team forms."""
@@ -180,6 +234,7 @@ def test_stream_that_may_use_half_the_cus():
     mask = (C.c_uint32 * words)(*[0x55555555] * words)
     h = C.c_void_p()
     if hip.hipExtStreamCreateWithCUMask(C.byref(h), words, mask) != 0:
+        hip.hipGetLastError()  # or the next call reports it
         pytest.skip("the driver here makes no streams with a CU mask")
     A = near_diagonal(131072, 4)
     b = A.scipy() @ np.random.default_rng(5).uniform(-1, 1, A.n)
