@@ -48,7 +48,7 @@ struct TeamArgs {
     int32_t max_iters, max_cycles, literal;
     int32_t hist_cap;    // entries of hist; the launch ends when a cycle may not fit
     int32_t resume;      // the counters continue from *st
-    int32_t batch;       // one of many systems: counted as the batch counts
+    int32_t batch;       // one of many systems: what the batch does and counts where it differs
     int32_t format;      // basis format (launches of many systems)
     int32_t wait_us;     // the team's workgroups come within this time or not at all (0: not at all)
     uint32_t epoch0;     // tags of this solve are above it; the slots hold none that are

@@ -769,6 +769,10 @@ __device__ __forceinline__ void team_solve(int rank, TeamShared& S) {
                 nonfinite = over = true;
                 status = CB_ERR_NONFINITE;
                 bd = 0;
+                if (x.arg(&TeamArgs::batch)) {  // (the batch leaves x as the cycle found it)
+                    stop = 1;
+                    break;
+                }
             } else {
                 // the new rotation and g, by every thread from the same values
                 if (hn == 0.0) bd = 1;

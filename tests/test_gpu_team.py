@@ -116,6 +116,30 @@ def test_batch_over_several_launches():
         assert np.array_equal(alone[2].cpu().numpy(), x), sizes[i]
 
 
+def test_batch_keeps_x_of_a_cycle_that_overflows():
+    """Row 5 of I + L has an entry of 1e200, which step 5 from b = e_0 meets: the
+    norm overflows, and x is still what the cycle began with, with and without
+    teams."""
+    n = 600
+    i = np.arange(n)
+    col = np.concatenate([[0], np.stack([i[:-1], i[1:]], 1).ravel()]).astype(np.int32)
+    val = np.ones(col.size)
+    val[1 + 2 * 4] = 1e200  # (5, 4)
+    rp = np.concatenate([[0], 2 * i + 1]).astype(np.int32)
+    Ad = cb.DeviceCSR.from_host(rp, col, val)
+    b = torch.zeros(n, dtype=torch.float64, device="cuda")
+    b[0] = 1.0
+    for wait in (-1, 0):
+        cb.lib().cb_internal_team_wait(wait, 0)
+        try:
+            x = torch.zeros(n, dtype=torch.float64, device="cuda")
+            r = cb.cbgmres_solve_batch([(Ad, b, x, 30, 1e-10, "float64")])[0]
+        finally:
+            cb.lib().cb_internal_team_wait(-1, 0)
+        assert r["status"] == cb.CB_ERR_NONFINITE and r["iterations"] == 4 and r["restarts"] == 1
+        assert r["rel_residual"] == 1.0 and not x.any()
+
+
 def test_batch_does_not_wait_for_its_slow_systems_in_turn():
     """1280 one-workgroup systems, five times what the GPU holds, of which every
     256th runs 2000 steps (a tolerance it cannot meet): the slow ones run side by
