@@ -290,6 +290,37 @@ __device__ __forceinline__ void load_entries(const Ctx& x, const double* val, in
         }
     }
 }
+// The rows of a block of which one has most of the entries, more than fit the
+// staging buffer: the wave takes the run in pieces, values and operands staged
+// side by side, and each lane adds what a piece holds of its row, in CSR order.
+// That is one entry at a time of the block, from LDS, against one at a time of
+// each row, from memory, which takes four times as long: n = 500,000 with one row
+// of 300,000 entries 8182 -> 1979 ms (7499 by one launch per operation).  So it
+// pays where a row has a quarter of the block's entries; rows of 200 entries
+// each, 4096 of them, take 8.0 ms a lane per row and 14.5 so.
+__device__ __forceinline__ void long_rows(const Ctx& x, const double* val, const double* xs, double d, int c0, int c1,
+                                          int k0, int k1, double* stage, double& s) {
+    constexpr int H = kStage / 2, C = H / 64;
+    const int32_t* ci = x.arg(&TeamArgs::ci);
+    for (int q = k0; q < k1; q += H) {
+        double vv[C], xv[C];
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const int k = min(q + c * 64 + x.lane, k1 - 1);
+            vv[c] = val[k];
+            xv[c] = ld_ctl(xs + ci[k]);
+        }
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            stage[c * 64 + x.lane] = vv[c];
+            stage[H + c * 64 + x.lane] = xv[c] / d;
+        }
+        __builtin_amdgcn_wave_barrier();
+        const int end = min(c1, q + H);
+        for (int k = max(c0, q); k < end; ++k) s = fma(stage[k - q], stage[H + k - q], s);
+        __builtin_amdgcn_wave_barrier();
+    }
+}
 // S.w = A (xs / d), or b - A (xs / d), over the workgroup's rows: as
 // spmv_rows_staged (64 rows a wave, products staged in LDS, each row summed in
 // CSR order), the operand read with device-scope loads since other workgroups
@@ -322,8 +353,12 @@ __device__ __forceinline__ void team_spmv(Ctx& x, Entries& e, const double* val,
             for (int k = c0; k < c1; ++k) s += prod[k - k0];
             __builtin_amdgcn_wave_barrier();
         } else {
-            const int32_t* ci = x.arg(&TeamArgs::ci);
-            for (int k = c0; k < c1; ++k) s = fma(val[k], ld_ctl(xs + ci[k]) / d, s);
+            if (__any(c1 - c0 >= (k1 - k0) / 4)) {
+                long_rows(x, val, xs, d, c0, c1, k0, k1, prod, s);
+            } else {
+                const int32_t* ci = x.arg(&TeamArgs::ci);
+                for (int k = c0; k < c1; ++k) s = fma(val[k], ld_ctl(xs + ci[k]) / d, s);
+            }
             if (blk + kTW < nblk) load_entries(x, val, blk + kTW, e);
         }
         x.S.w[padded(blk * 64 + x.lane)] = b ? bv - s : s;  // rows past n: 0

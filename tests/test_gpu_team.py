@@ -23,9 +23,9 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 
-def near_diagonal(n, seed, wide_row=None):
+def near_diagonal(n, seed, wide_row=None, width=600):
     """Rows of 4 on the diagonal with up to four neighbours at distances 1 and
-    37; row wide_row (if given) has 600 entries of 1/600."""
+    37; row wide_row (if given) has `width` entries of 1/width."""
     rng = np.random.default_rng(seed)
     i = np.arange(n)
     offs = np.array([-37, -1, 0, 1, 37])
@@ -37,8 +37,8 @@ def near_diagonal(n, seed, wide_row=None):
     c, v = cols[keep], vals[keep]
     if wide_row is not None:
         off = rows != wide_row
-        wide = np.unique(np.append(rng.choice(n, 600, replace=False), wide_row))
-        wv = np.full(wide.size, 1.0 / 600)
+        wide = np.unique(np.append(rng.choice(n, width, replace=False), wide_row))
+        wv = np.full(wide.size, 1.0 / width)
         wv[wide == wide_row] = 4.0
         at = np.searchsorted(rows, wide_row)
         rows = np.concatenate([rows[:at], np.full(wide.size, wide_row), rows[at:][off[at:]]])
@@ -78,6 +78,36 @@ def test_edges(n, fmt):
 @pytest.mark.parametrize("n", [700, 20000])
 def test_long_row(n):
     check(near_diagonal(n, n, wide_row=n // 3), 30, "frsz2_32", n)
+
+
+@pytest.mark.parametrize("n,width,count", [(3000, 2999, 1), (700, 257, 1), (20000, 9000, 3), (400, 399, 400)])
+def test_rows_longer_than_the_staging_buffer(n, width, count):
+    """One row with most of its block's entries (staged in pieces of 256), in a
+    block of other long rows (a lane per row), and a dense matrix, alone and as a
+    batch, against the oracle's iterations and x."""
+    A = near_diagonal(n, n)
+    rng = np.random.default_rng(n)
+    M = A.scipy().tolil()
+    for r in rng.choice(n, count, replace=False):
+        c = rng.choice(n, width, replace=False)
+        M[r, c] = rng.uniform(-1, 1, width) / width
+        M[r, r] = 4.0
+    M = M.tocsr()
+    M.sort_indices()
+    A = synth.CSR(n, M.indptr.astype(np.int32), M.indices.astype(np.int32), M.data)
+    b = M @ rng.uniform(-1, 1, n)
+    ref = oracle.gmres(A, b, 30, 1e-10, "frsz2_32")
+    Ad, bd = cb.DeviceCSR.from_host(A.row_ptr, A.col, A.val), torch.from_numpy(b).cuda()
+    for batch in (False, True):
+        print(f"long rows n={n} width={width} count={count} batch={batch}", flush=True)
+        x = torch.zeros(n, dtype=torch.float64, device="cuda")
+        if batch:
+            res = cb.cbgmres_solve_batch([(Ad, bd, x, 30, 1e-10, "frsz2_32")])[0]
+        else:
+            res, _ = cb.cbgmres_solve(Ad, bd, x, 30, 1e-10, "frsz2_32")
+        assert res["converged"] and abs(res["iterations"] - ref.iterations) <= 1
+        assert np.linalg.norm(x.cpu().numpy() - ref.x) <= 1e-8 * np.linalg.norm(ref.x)
+        assert np.linalg.norm(b - M @ x.cpu().numpy()) <= 1e-10 * (1 + 1e-6) * np.linalg.norm(b)
 
 
 @pytest.mark.parametrize("m", [1, 2, 3, 104, 105])
