@@ -265,7 +265,10 @@ typedef struct cb_options {
                                   solve as one launch per operation; with 0, systems of
                                   up to 8 entries a row, about half a million rows and
                                   m <= 104 run as one launch of resident workgroups,
-                                  which sums in another order. */
+                                  which sums in another order.  (Alone that is the
+                                  faster one.  Above some 65,000 rows it takes most of
+                                  the GPU, so such solves from several host threads run
+                                  one after the other, while those of 1 and 2 overlap.) */
 } cb_options;
 
 typedef struct cb_result {

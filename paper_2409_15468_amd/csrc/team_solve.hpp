@@ -295,7 +295,7 @@ __device__ __forceinline__ void load_entries(const Ctx& x, const double* val, in
 // side by side, and each lane adds what a piece holds of its row, in CSR order.
 // That is one entry at a time of the block, from LDS, against one at a time of
 // each row, from memory, which takes four times as long: n = 500,000 with one row
-// of 300,000 entries 8182 -> 1979 ms (7499 by one launch per operation).  So it
+// of 300,000 entries 8182 -> 1983 ms (7499 by one launch per operation).  So it
 // pays where a row has a quarter of the block's entries; rows of 200 entries
 // each, 4096 of them, take 8.0 ms a lane per row and 14.5 so.
 __device__ __forceinline__ void long_rows(const Ctx& x, const double* val, const double* xs, double d, int c0, int c1,
