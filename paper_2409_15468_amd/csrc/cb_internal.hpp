@@ -38,7 +38,7 @@ constexpr int kDefaultMaxIters = 20000;
 // Largest row count: row indices, row-group starts and the 8-row groups past
 // them (up to 2048 * row_groups(n)) all stay below 2^31 in 32-bit arithmetic.
 constexpr int64_t kMaxRows = (int64_t(1) << 31) - 4096;
-// one-workgroup batched solver (batch.hip)
+// batched solver (team_batch.hip; batch.hip: one workgroup per system)
 constexpr int kBatchThreads = 512;
 constexpr int kBatchMaxN = 65536;
 constexpr int kBatchMaxRestart = 104;
@@ -49,7 +49,7 @@ int batch_without_teams(const cb_batch_item* items, int count, cb_result* result
 
 // Serving ring (team_ring.hip): a persistent launch that takes small systems
 // from descriptors published while it runs, a team of workgroups each.
-constexpr int kRingSlots = 512;       // systems in flight at most
+constexpr int kRingSlots = 1024;      // systems in flight at most (their exchange words: 55 KB each)
 constexpr int32_t kRingMaxN = 16384;  // rows of a system at most
 struct BatchRing;
 // Pinned/mapped/coherent control block, descriptors and results; NULL on failure.

@@ -318,6 +318,26 @@ def test_stream_that_may_use_half_the_cus():
         assert hip.hipStreamDestroy(h) == 0
 
 
+def test_a_thousand_small_requests_in_flight():
+    """1000 requests that run 20000 steps each (a tolerance they cannot meet):
+    the device-resident loop takes them all at once, and ends them all."""
+    A = synth.convection_diffusion(4, 2, (20.0, 0.0))
+    b = synth.rhs_from_solution(A, np.random.default_rng(1).uniform(-1, 1, A.n))
+    srv = cb.Server(4 << 30, 0, lanes=1)
+    tickets = [srv.submit(A.row_ptr, A.col, A.val, b, 2, 1e-30, "float64") for _ in range(1000)]
+    running, t0, got = 0, time.time(), {}
+    while len(got) < len(tickets) and time.time() - t0 < 60:
+        running = max(running, srv.stats()[2])
+        for t in tickets:
+            if t not in got and (r := srv.poll(t, A.n)) is not None:
+                got[t] = r
+        time.sleep(0.002)
+    srv.close()
+    print(f"{running} at once, {time.time() - t0:.2f} s", flush=True)
+    assert len(got) == 1000 and running > 900
+    assert {(r[1]["status"], r[1]["iterations"]) for r in got.values()} == {(cb.CB_ERR_NOT_CONVERGED, 20000)}
+
+
 def test_served_small_then_large():
     """A small request starts the serving launch (128 workgroups); the larger
     ones after it need 138 and 256 of the GPU's CUs, so they run only if
