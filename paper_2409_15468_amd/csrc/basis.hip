@@ -574,28 +574,11 @@ bool launch_project_column(int fmt, const cb_basis& V, int j, const double* w, d
     return true;
 }
 
-int launch_subtract(int fmt, const cb_basis& V, int j, const int* jdev, const double* h,
-                     double* w, double* partials, const int* guard, int sign, const Epi& e,
-                     hipStream_t s) {
-    BasisView b = view_of(V);
-    const int G = project_groups(V.n);
-    dim3 grid((unsigned)G);
-    Epi ee = e;
-    ee.G = G;
-    ee.ncols = 1;
-    ee.cw = 1;
-    // with the count on the device, size the policy for the largest count j
-    const int stream = streams_basis(b, j);
-    CB_DISPATCH(fmt, (k_subtract<F, 4><<<grid, kThreads, 0, s>>>(b, j, jdev, h, w, partials, sign, stream,
-                                                                guard, ee)));
-    return G;
-}
-
 // Workgroups of `kernel` the current device holds at once (its occupancy per
 // CU times the CU count), cached per device and kernel; 0 if the runtime
 // cannot say.
 static int resident_groups(const void* kernel, int id, int threads) {
-    constexpr int kDevs = 16, kIds = 96;
+    constexpr int kDevs = 16, kIds = 112;
     static std::atomic<int> cache[kDevs][kIds];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kDevs || id < 0 || id >= kIds) return 0;
@@ -608,6 +591,29 @@ static int resident_groups(const void* kernel, int id, int threads) {
     r = cus * per_cu;
     if (r > 0) cache[dev][id].store(r, std::memory_order_relaxed);
     return r;
+}
+
+int launch_subtract(int fmt, const cb_basis& V, int j, const int* jdev, const double* h,
+                     double* w, double* partials, const int* guard, int sign, const Epi& e,
+                     hipStream_t s) {
+    BasisView b = view_of(V);
+    int G = project_groups(V.n);
+    // Whole rounds of resident workgroups: three frsz2_21 ones fit a CU, and 1024
+    // ran as 768 and then 256, one to a CU, 982 us at 2^24 x 101 where 768 that loop
+    // over the row groups take 907 (frsz2_12 734 and 633; two or four to a CU: as before).
+    int R = 0;
+    CB_DISPATCH(fmt, (R = resident_groups(reinterpret_cast<const void*>(&k_subtract<F, 4>), 96 + F, kThreads)));
+    if (R > 0 && G > R) G = G / R * R;
+    dim3 grid((unsigned)G);
+    Epi ee = e;
+    ee.G = G;
+    ee.ncols = 1;
+    ee.cw = 1;
+    // with the count on the device, size the policy for the largest count j
+    const int stream = streams_basis(b, j);
+    CB_DISPATCH(fmt, (k_subtract<F, 4><<<grid, kThreads, 0, s>>>(b, j, jdev, h, w, partials, sign, stream,
+                                                                guard, ee)));
+    return G;
 }
 
 // Columns up to which the solver's launches read them twice: an inner solve of 11

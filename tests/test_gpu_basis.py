@@ -152,3 +152,20 @@ def test_project_of_short_vectors(fmt, n, j):
     w = np.random.default_rng(j).standard_normal(n)
     h = cb.cb_cgs_project(V, j, torch.from_numpy(w).cuda()).cpu().numpy()
     assert np.all(np.abs(h - oracle.cgs_project(dec, w)) <= 1e-12 * (np.abs(dec).T @ np.abs(w)) + 1e-300)
+
+
+@pytest.mark.parametrize("fmt", ["frsz2_21", "frsz2_12", "frsz2_32", "frsz2_16"])
+def test_update_of_more_row_groups_than_workgroups(fmt):
+    """Above 2^21 rows the update's workgroups, whole rounds of what the GPU
+    holds at once, loop over the row groups, and the last is ragged: w within 1e-14
+    of |w| + sum |h_i v_ik| and the norm within 1e-13 of the oracle's."""
+    n, j = 2048 * 1100 + 37, 5
+    V, _, dec = build_basis(fmt, n, j, seed=13)
+    rng = np.random.default_rng(14)
+    w, h = rng.standard_normal(n), rng.standard_normal(j)
+    wd, norm2 = torch.from_numpy(w).cuda(), torch.empty(1, dtype=torch.float64, device="cuda")
+    cb.cb_cgs_subtract(V, j, torch.from_numpy(h).cuda(), wd, norm2=norm2)
+    ref = oracle.cgs_subtract(dec, h, w)
+    assert np.all(np.abs(wd.cpu().numpy() - ref) <= 1e-14 * (np.abs(w) + np.abs(dec) @ np.abs(h)))
+    nr = oracle.dot(ref, ref)
+    assert abs(norm2.item() - nr) <= 1e-13 * nr
