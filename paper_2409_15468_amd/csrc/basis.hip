@@ -574,14 +574,18 @@ bool launch_project_column(int fmt, const cb_basis& V, int j, const double* w, d
     return true;
 }
 
+constexpr int kFewCus = 32;  // CUs of the smallest partition of the GPU: so many workgroups are one round
+static int current_device() {
+    int dev = 0;
+    return hipGetDevice(&dev) == hipSuccess ? dev : -1;
+}
 // Workgroups of `kernel` the current device holds at once (its occupancy per
 // CU times the CU count), cached per device and kernel; 0 if the runtime
 // cannot say.
-static int resident_groups(const void* kernel, int id, int threads) {
+static int resident_groups(const void* kernel, int id, int threads, int dev) {
     constexpr int kDevs = 16, kIds = 112;
     static std::atomic<int> cache[kDevs][kIds];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kDevs || id < 0 || id >= kIds) return 0;
+    if (dev < 0 || dev >= kDevs || id < 0 || id >= kIds) return 0;
     int r = cache[dev][id].load(std::memory_order_relaxed);
     if (r > 0) return r;
     int cus = 0, per_cu = 0;
@@ -602,7 +606,9 @@ int launch_subtract(int fmt, const cb_basis& V, int j, const int* jdev, const do
     // ran as 768 and then 256, one to a CU, 982 us at 2^24 x 101 where 768 that loop
     // over the row groups take 907 (frsz2_12 734 and 633; two or four to a CU: as before).
     int R = 0;
-    CB_DISPATCH(fmt, (R = resident_groups(reinterpret_cast<const void*>(&k_subtract<F, 4>), 96 + F, kThreads)));
+    if (G > kFewCus)
+        CB_DISPATCH(fmt, (R = resident_groups(reinterpret_cast<const void*>(&k_subtract<F, 4>), 96 + F, kThreads,
+                                              current_device())));
     if (R > 0 && G > R) G = G / R * R;
     dim3 grid((unsigned)G);
     Epi ee = e;
@@ -622,36 +628,54 @@ int launch_subtract(int fmt, const cb_basis& V, int j, const int* jdev, const do
 // (The primitive's launches, hot in the cache, are faster read once at any count.)
 constexpr int kFewColumns = 12;
 
-// capacity: doubles of `partials`.
+// What the exchange between a tile's waves costs a round of the one-read kernel,
+// in columns: frsz2_32 at 500009 x 8 takes 12.6 us with W = 1 and 14.0 with 2, one
+// round each, and at 300007 x 17 17.1 and 13.7.
+constexpr int kExchangeColumns = 4;
+
+// Workgroups of that kernel with W waves a tile: what the GPU holds, cut to the
+// partial sums there is room for (capacity doubles) and to the fewest that take
+// the same number of rounds over the tiles.
+struct SubProjGrid {
+    int G;
+    int64_t rounds;
+};
 template <int FMT, int W, int N>
-static int run_subtract_project(const BasisView& b, int j, const double* h, double* w, double* partials,
-                                int64_t capacity, const int* guard, Epi e, hipStream_t s) {
+static SubProjGrid sub_proj_grid(const BasisView& b, int j, int64_t capacity, int dev) {
     constexpr int threads = sub_proj_threads(W), T = threads / 64 / W;
     const int ngroups = ((b.np + kTile - 1) / kTile + T - 1) / T;
     const int R = resident_groups(reinterpret_cast<const void*>(&k_subtract_project<FMT, W, N>),
-                                  FMT * 5 + (W > 1) + (W > 2) + (W > 4) + (N < kResidentColumns<FMT> ? 4 : 0), threads);
+                                  FMT * 5 + (W > 1) + (W > 2) + (W > 4) + (N < kResidentColumns<FMT> ? 4 : 0), threads,
+                                  dev);
     int64_t G = R > 0 ? R : 256;
     if (G > capacity / (j + 1)) G = capacity / (j + 1);
     if (G > kTicketGroup * kMaxTicketGroups) G = kTicketGroup * kMaxTicketGroups;
-    // as few workgroups as take the same number of rounds over the tiles
     const int64_t rounds = (ngroups + G - 1) / G;
     G = (ngroups + rounds - 1) / rounds;
-    e.G = (int)G;
+    return {(int)G, rounds};
+}
+template <int FMT, int W, int N>
+static int run_subtract_project(const BasisView& b, int j, const double* h, double* w, double* partials,
+                                int64_t capacity, int dev, const int* guard, Epi e, hipStream_t s) {
+    const int G = sub_proj_grid<FMT, W, N>(b, j, capacity, dev).G;
+    e.G = G;
     e.ncols = j + 1;  // u_0 .. u_{j-1} and the norm
     e.cw = j + 1;
-    k_subtract_project<FMT, W, N><<<(unsigned)G, threads, 0, s>>>(b, j, h, w, partials, guard, e);
-    return (int)G;
+    k_subtract_project<FMT, W, N><<<(unsigned)G, sub_proj_threads(W), 0, s>>>(b, j, h, w, partials, guard, e);
+    return G;
 }
 
 int launch_subtract_project(int fmt, const cb_basis& V, int j, const double* h, double* w, double* partials,
                             int64_t capacity, const int* guard, const Epi& e, hipStream_t s) {
     BasisView b = view_of(V);
+    const int dev = current_device();
     int G = 0;
     if (e.mode != EPI_PARTIALS && j <= kFewColumns) {
         G = project_groups(V.n);
         CB_DISPATCH(fmt, ({
             // whole waves of resident workgroups
-            const int R = resident_groups(reinterpret_cast<const void*>(&k_subtract_project_few<F, 4>), 80 + F, kThreads);
+            const int R = resident_groups(reinterpret_cast<const void*>(&k_subtract_project_few<F, 4>), 80 + F, kThreads,
+                                          dev);
             if (R > 0 && G > R) G = G / R * R;
             Epi ee = e;
             ee.G = G;
@@ -664,26 +688,32 @@ int launch_subtract_project(int fmt, const cb_basis& V, int j, const double* h, 
     CB_DISPATCH(fmt, ({
         constexpr int N = kResidentColumns<F>;
         // among the W whose waves hold the columns (8 if none does) the one with
-        // the fewest rounds over the tiles, each as long as a wave has columns;
-        // the smallest such W
-        const int64_t tiles = (b.np + kTile - 1) / kTile;
-        int W = 8;
+        // the fewest rounds over the tiles, each as long as a wave has columns and,
+        // with more than one wave, an exchange; the smallest such W.  The rounds are
+        // those of the grids that will run, whose partial sums have to fit
+        // (reckoned with 2048 resident waves and no exchange, frsz2_16 at 200003 x 40
+        // took 24.4 us, now 20.0; two reads of the columns 21.3)
+        int W = 0;
         int64_t best = INT64_MAX;
-        for (int v = 1; v <= 8; v *= 2) {
-            const int64_t cost = (tiles * v + kResidentWaves - 1) / kResidentWaves * ((j + v - 1) / v);
-            if ((N * v >= j || v == 8) && cost < best) {
+        auto weigh = [&](int v, int64_t rounds) {
+            const int64_t cost = rounds * ((j + v - 1) / v + (v > 1 ? kExchangeColumns : 0));
+            if (cost < best) {
                 best = cost;
                 W = v;
             }
-        }
+        };
+        if (N >= j) weigh(1, sub_proj_grid<F, 1, N>(b, j, capacity, dev).rounds);
+        if (2 * N >= j) weigh(2, sub_proj_grid<F, 2, N>(b, j, capacity, dev).rounds);
+        if (4 * N >= j) weigh(4, sub_proj_grid<F, 4, N>(b, j, capacity, dev).rounds);
+        weigh(8, sub_proj_grid<F, 8, N>(b, j, capacity, dev).rounds);
         // few columns in fewer registers, where a third workgroup then fits a CU
-        // (frsz2_16 in the n = 2^21 inner solve: 18.6 -> 17.6 us a step)
+        // (2^21 x 8: float32 22.4 -> 21.8 us, frsz2_16 21.8 -> 21.4)
         constexpr int Few = N > 13 ? 8 : N;
-        if (W == 1 && j <= Few) G = run_subtract_project<F, 1, Few>(b, j, h, w, partials, capacity, guard, e, s);
-        else if (W == 1) G = run_subtract_project<F, 1, N>(b, j, h, w, partials, capacity, guard, e, s);
-        else if (W == 2) G = run_subtract_project<F, 2, N>(b, j, h, w, partials, capacity, guard, e, s);
-        else if (W == 4) G = run_subtract_project<F, 4, N>(b, j, h, w, partials, capacity, guard, e, s);
-        else G = run_subtract_project<F, 8, N>(b, j, h, w, partials, capacity, guard, e, s);
+        if (W == 1 && j <= Few) G = run_subtract_project<F, 1, Few>(b, j, h, w, partials, capacity, dev, guard, e, s);
+        else if (W == 1) G = run_subtract_project<F, 1, N>(b, j, h, w, partials, capacity, dev, guard, e, s);
+        else if (W == 2) G = run_subtract_project<F, 2, N>(b, j, h, w, partials, capacity, dev, guard, e, s);
+        else if (W == 4) G = run_subtract_project<F, 4, N>(b, j, h, w, partials, capacity, dev, guard, e, s);
+        else G = run_subtract_project<F, 8, N>(b, j, h, w, partials, capacity, dev, guard, e, s);
     }));
     return G;
 }

@@ -107,3 +107,11 @@ def test_columns_kept_in_registers(fmt, n, j):
     registers, past them, with fewer columns than waves and with a last tile of
     one block; 1100000 rows are enough tiles for one and two waves each."""
     check(fmt, n, j, 7 * j + n % 97)
+
+
+@pytest.mark.parametrize("fmt", ["frsz2_32", "frsz2_21", "float32", "float64"])
+@pytest.mark.parametrize("n,j", [(200003, 8), (200003, 14), (200003, 40), (700001, 8), (700001, 17), (700001, 40)])
+def test_grids_cut_by_the_partial_sums(fmt, n, j):
+    """Sizes at which the workspace holds fewer partial sums than the GPU holds
+    workgroups, so that 1, 2, 4 and 8 waves a tile take several rounds each."""
+    check(fmt, n, j, 3 * j + n % 89)
