@@ -423,7 +423,7 @@ __global__ __launch_bounds__(sub_proj_threads(W), 2) void k_subtract_project(Bas
 // The same for the few columns of a solver step's start, each read twice, the
 // second time from the cache: one wave per tile and no registers held.  In a
 // solve the data come from HBM behind the SpMV, and what counts is how soon
-// the loads go out.
+// the loads go out (launch_subtract_project says when).
 // At most 256 registers (two waves per SIMD): with one, a launch of more
 // workgroups than CUs runs in two rounds and pays its start-up twice.
 template <int FMT, int U>
@@ -622,11 +622,17 @@ int launch_subtract(int fmt, const cb_basis& V, int j, const int* jdev, const do
     return G;
 }
 
-// Columns up to which the solver's launches read them twice: an inner solve of 11
-// steps on n = 2^21 banded rows, frsz2_16, refined to 1e-12, takes 10.39 ms so and
-// 10.53 by the one-read kernel; the n = 10^6 GMRES(100) 59.5 ms either way.
-// (The primitive's launches, hot in the cache, are faster read once at any count.)
+// The solver's launches read few columns twice: up to 12 that together take up to
+// 56 MB, but of float64.  From traces of solves with n = 2^15 to 2^22, banded and
+// stencil, six formats, each step by both kernels: over the first 12 steps of a
+// cycle this choice is 1.9% above the faster kernel at each step, one read always
+// 6.9%, 12 columns of any size 6.7% (us a step, one read / two: n = 2^19 x 8
+// frsz2_16 15.8 / 13.5, frsz2_32 16.8 / 14.1; 2^21 x 11 frsz2_16 32.0 / 28.7, 2^21 x 8
+// float32 27.9 / 34.4, float64 36.1 / 52.2; 2^15 x 16 frsz2_32 13.1 / 14.7).  Over 100
+// steps either choice is within 1.3%.  (The primitive's launches, hot in the
+// cache, are faster read once at any count.)
 constexpr int kFewColumns = 12;
+constexpr int64_t kFewBytes = 56000000;
 
 // What the exchange between a tile's waves costs a round of the one-read kernel,
 // in columns: frsz2_32 at 500009 x 8 takes 12.6 us with W = 1 and 14.0 with 2, one
@@ -670,18 +676,21 @@ int launch_subtract_project(int fmt, const cb_basis& V, int j, const double* h, 
     BasisView b = view_of(V);
     const int dev = current_device();
     int G = 0;
-    if (e.mode != EPI_PARTIALS && j <= kFewColumns) {
+    if (e.mode != EPI_PARTIALS && j <= kFewColumns && j * (b.col_bytes + 4 * b.exp_stride) <= kFewBytes &&
+        fmt != CB_F64) {
         G = project_groups(V.n);
         CB_DISPATCH(fmt, ({
-            // whole waves of resident workgroups
-            const int R = resident_groups(reinterpret_cast<const void*>(&k_subtract_project_few<F, 4>), 80 + F, kThreads,
-                                          dev);
-            if (R > 0 && G > R) G = G / R * R;
-            Epi ee = e;
-            ee.G = G;
-            ee.ncols = j + 1;
-            ee.cw = j + 1;
-            k_subtract_project_few<F, 4><<<G, kThreads, 0, s>>>(b, j, h, w, partials, guard, ee);
+            if constexpr (F != CB_F64) {
+                // whole waves of resident workgroups
+                const int R = resident_groups(reinterpret_cast<const void*>(&k_subtract_project_few<F, 4>), 80 + F,
+                                              kThreads, dev);
+                if (R > 0 && G > R) G = G / R * R;
+                Epi ee = e;
+                ee.G = G;
+                ee.ncols = j + 1;
+                ee.cw = j + 1;
+                k_subtract_project_few<F, 4><<<G, kThreads, 0, s>>>(b, j, h, w, partials, guard, ee);
+            }
         }));
         return G;
     }

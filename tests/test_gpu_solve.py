@@ -253,6 +253,27 @@ def test_long_cycle_of_fused_steps(fmt, m):
     np.testing.assert_allclose(res["rel_residual"], ref.rel_residual, rtol=1e-2)
 
 
+@pytest.mark.parametrize("fmt", ["frsz2_32", "frsz2_21", "frsz2_16", "float32", "float16", "frsz2_12", "frsz2b64_16", "float64"])
+@pytest.mark.parametrize("n", [2000, 20011])
+def test_fused_steps_around_twelve_columns(fmt, n):
+    """One cycle of 16 fused steps, launch by launch: the solver's two kernels
+    for the first update and second projection change over behind step 12 (float64
+    and the primitive have one), and each keeps u or drops it (eta = 0.7 and 1e-9).
+    The history follows the oracle's to what the format's rounding lets it drift."""
+    A = dominant_random(n, 10.0, seed=n + 1)
+    b = A.scipy() @ np.random.default_rng(n + 2).uniform(-1.0, 1.0, n)
+    for eta in (0.7, 1e-9):
+        kw = dict(eta=eta, max_iters=16)
+        res, x, hist = gpu_solve(A, b, 16, 1e-14, fmt, fuse_updates=2, history_cap=16, **kw)
+        ref = oracle.gmres(A, b, 16, 1e-14, fmt, hist_cap=16, **kw)
+        unit = UNIT.get(fmt) or 2.0 ** -(int(fmt.split("_")[1]) - 2)
+        k = min(hist.size, ref.history.size)
+        assert k >= 13 and res["reorths"] == ref.reorths
+        # above what the stored columns' truncation, 64 units of it a step, adds
+        np.testing.assert_allclose(hist[:k], ref.history[:k], rtol=1e-6, atol=64 * unit * ref.history[0])
+        assert np.linalg.norm(x - ref.x) <= (1e-8 + 64 * unit) * np.linalg.norm(ref.x)
+
+
 @pytest.mark.parametrize("fmt", ["frsz2_21", "float32", "float64"])
 @pytest.mark.parametrize("fuse", [1, 2])
 def test_fused_and_separate_first_update(fmt, fuse):
