@@ -336,7 +336,8 @@ void fill_result(cb_result* res, const State& hs, double seconds) {
 // no team for it or no launch of one (more) could run: x is then what *done says
 // has been done of the solve.  The exchange slots take the place of w2 (or of the
 // partial sums, for the smallest systems) and the history of a launch, if the
-// caller wants one, that of H, so the workspace is that of the other path.
+// caller wants one, that of H and what follows it, so the workspace is that of the
+// other path.
 static int solve_team(const cb_csr& A, const double* b, double* x, int m, int fmt, const Ws& W, const TeamArgs& opts,
                       const double* dinv, const double* pval, double* history_host, int64_t history_cap,
                       cb_result* res, double t0, Carry* done, hipStream_t s) {
@@ -362,7 +363,8 @@ static int solve_team(const cb_csr& A, const double* b, double* x, int m, int fm
     a.st = W.at<State>(W.L.state);
     const bool history = history_host && history_cap > 0;
     a.hist = history ? W.at<double>(W.L.H) : nullptr;
-    a.hist_cap = history ? (m + 1) * m : INT32_MAX - 2 * kTeamMaxRestart;
+    // (H and the vectors behind it, which a team keeps in LDS: 224 steps or more)
+    a.hist_cap = history ? (int32_t)((W.L.w - W.L.H) / 8) : INT32_MAX - 2 * kTeamMaxRestart;
     a.n = n;
     a.m = m;
     a.G = sh.G;
