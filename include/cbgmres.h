@@ -444,7 +444,7 @@ int cb_intensity_run(const cb_basis* V, int32_t col, int32_t ops, double a, doub
  * not depend on the rest of the batch (the team and its reduction order follow
  * from the system's rows); it may differ in the last bits from cbgmres_solve
  * on the same system, whose reductions are ordered otherwise.  (A system whose
- * team does not come together within 0.1 s, because other programs' work holds
+ * team does not come together within 0.5 s, because other programs' work holds
  * the GPU's CUs, is solved by one workgroup, as if no team had been tried.)
  * ====================================================================== */
 typedef struct cb_batch_item {
@@ -499,7 +499,7 @@ int cbgmres_solve_batch(const cb_batch_item* items, int32_t count, const cb_opti
  * wait behind large ones.  The path depends on a request's shape only and
  * neither path's arithmetic depends on the other requests, so a result is the
  * same, bit for bit, alone and in any mix.  (Where other programs' work on the
- * GPU keeps a team of workgroups from coming together, within 0.1 s, the request
+ * GPU keeps a team of workgroups from coming together, within 0.5 s, the request
  * is solved without one and may differ in the last bits.)
  * ====================================================================== */
 typedef struct cb_server cb_server;

@@ -524,6 +524,11 @@ int solve_by_teams(const cb_batch_item* items, int count, const BatchOpts& o, cb
         (void)hipFreeAsync(mem, s);
         if (hipStreamSynchronize(s) != hipSuccess && st == CB_OK) st = fail(CB_ERR_HIP, "batch solve failed");
     }
+    if (st == CB_OK) {
+        bool formed = true;
+        for (int i : order) formed = formed && states[i].status != kTeamAbandoned;
+        team_waited(formed);
+    }
     for (int i : order) {
         if (st != CB_OK) break;
         if (states[i].status == kTeamLost &&

@@ -384,6 +384,7 @@ static int solve_team(const cb_csr& A, const double* b, double* x, int m, int fm
         const bool keep = history && recorded < history_cap;
         if (keep) CB_HIP(hipMemcpyAsync(hh, a.hist, (size_t)a.hist_cap * 8, hipMemcpyDeviceToHost, s));
         CB_HIP(hipStreamSynchronize(s));
+        team_waited(hs->status != kTeamAbandoned);
         if (hs->status == kTeamAbandoned) return kTeamAbandoned;
         done->iters = hs->iters;
         done->cycles = hs->cycles;

@@ -132,12 +132,14 @@ int64_t team_ll_words(int G, int m) {
     return kJoinWords + (G <= kDirect ? (int64_t)4 * G * (m + 2) : (int64_t)2 * (G + 1) * (m + 2));
 }
 
-static thread_local int32_t g_wait_us = -1, g_wait_skip = 0;
+static thread_local int32_t g_wait_us = -1, g_wait_skip = 0, g_missed = 0;
 int32_t team_wait_setting() { return g_wait_us; }
 int32_t team_wait_us() {
-    if (g_wait_us < 0 || g_wait_skip-- > 0) return kTeamWaitUs;
-    return g_wait_us;
+    if (g_wait_us >= 0 && g_wait_skip-- <= 0) return g_wait_us;
+    const int32_t us = kTeamWaitUs >> 2 * g_missed;
+    return us > kTeamWaitLeastUs ? us : kTeamWaitLeastUs;
 }
+void team_waited(bool formed) { g_missed = formed ? 0 : g_missed < 8 ? g_missed + 1 : 8; }
 
 void launch_team_clear(uint64_t* ll, int64_t words, hipStream_t s) {
     k_team_clear<<<(unsigned)((words + 255) / 256), 256, 0, s>>>(ll, words);
@@ -167,7 +169,11 @@ void launch_team(int fmt, const TeamArgs& a, hipStream_t s) {
 
 }  // namespace cb
 
-// (for tests)
+// (for tests) The wait after a team that formed or did not.
+extern "C" int32_t cb_internal_team_waited(int32_t formed) {
+    cb::team_waited(formed != 0);
+    return cb::team_wait_us();
+}
 extern "C" int32_t cb_internal_team_seats(int32_t groups, int32_t capacity) { return cb::seats_of(groups, capacity); }
 
 // How long the teams of this host thread's solves wait for their workgroups, in

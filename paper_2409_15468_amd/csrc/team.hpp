@@ -15,12 +15,15 @@ constexpr int kTeamAbandoned = -1;
 // (its queue was taken off the GPU): x holds each row before or after the last
 // cycle's update, the counters are those of the cycles before
 constexpr int kTeamLost = -2;
-// How long a team may take to come together before its solve goes the other
-// way: longer than any kernel of this library that may be in its way, at the
-// sizes that fit the GPU's memory many times (a projection of 2^24 x 101 takes 1
-// ms), short against what a caller whose GPU never has room would wait for each
-// solve.
-constexpr int32_t kTeamWaitUs = 100000;
+// How long a team may take to come together before its solve goes the other way.
+// Kernels of the process's other streams end (the longest of this library take
+// milliseconds), and waiting for them keeps a result independent of them; what
+// never ends, a resident kernel of another program, should not cost every
+// solve that time.  So each team in a row that does not form cuts the next
+// one's wait to a quarter, down to kTeamWaitLeastUs, for the host thread whose
+// solves they are, and one that forms restores it.
+constexpr int32_t kTeamWaitUs = 500000;
+constexpr int32_t kTeamWaitLeastUs = 2000;
 constexpr int kJoinWords = 16;  // ahead of the exchange slots, in a line of its own
 
 struct State;
@@ -71,9 +74,10 @@ inline void team_exchange(TeamArgs& a, uint64_t* p) {
     a.join = reinterpret_cast<unsigned*>(p);
     a.ll = p + kJoinWords;
 }
-// kTeamWaitUs, or what cb_internal_team_wait has set for the next launch of this
-// host thread.
+// The wait of this host thread's next launch: by kTeamWaitUs, or what
+// cb_internal_team_wait has set; and what came of one.
 int32_t team_wait_us();
+void team_waited(bool formed);
 int32_t team_wait_setting();
 // Clear the words at a.join and start the team on stream s.
 void launch_team(int fmt, const TeamArgs& a, hipStream_t s);

@@ -314,6 +314,7 @@ bool ring_poll(BatchRing* r, uint32_t seq, cb_result* res, uint32_t* launch, boo
     const int slot = (int)seq;
     if (__atomic_load_n(&r->ctl->done[slot], __ATOMIC_ACQUIRE) != r->seq_of[slot] + 1u) return false;
     const State& st = r->results[slot];
+    team_waited(st.status != kTeamAbandoned);
     *solved = st.status != kTeamAbandoned && st.status != kTeamLost;
     if (res) fill_result(res, st, 0.0);
     // (a lost team may have used tags past those its first workgroup reports, one

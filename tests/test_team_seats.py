@@ -1,5 +1,7 @@
-"""The seats that teams of workgroups reserve (host code, no GPU needed)."""
+"""The seats that teams of workgroups reserve and the time they are waited for
+(host code, no GPU needed)."""
 import itertools
+import threading
 
 import paper_2409_15468_amd as cb
 
@@ -19,3 +21,17 @@ def test_teams_that_are_seated_together_fit_every_xcd():
     for g in (1, 8, 9, 200, 249, 256):
         assert g <= seats(g, CUS) <= CUS
     assert seats(30, 30) == 30  # a device of fewer CUs seats the largest team it takes
+
+
+def test_wait_shrinks_while_teams_do_not_form():
+    """A quarter of half a second for each team in a row that does not form, 2 ms
+    at least, and all of it again after one that does; per host thread."""
+    waited = cb.lib().cb_internal_team_waited
+    assert waited(1) == 500000
+    assert [waited(0) for _ in range(12)] == [125000, 31250, 7812, 2000] + [2000] * 8
+    other = []
+    t = threading.Thread(target=lambda: other.append(waited(1)))
+    t.start()
+    t.join()
+    assert other == [500000] and waited(0) == 2000
+    assert waited(1) == 500000
