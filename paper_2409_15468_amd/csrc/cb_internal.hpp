@@ -98,7 +98,7 @@ inline bool generic_format(int f) {
     return (f >= CB_FRSZ2_BITS(3) && f <= CB_FRSZ2_BITS(32)) || generic_b64(f);
 }
 inline bool valid_format(int f) { return (f >= CB_F64 && f <= CB_FRSZ2_32_B64) || generic_format(f); }
-// formats the one-workgroup batched solver runs (the paper's block size 32)
+// formats the batched solver runs (the paper's block size 32)
 inline bool batch_format(int f) { return f >= CB_F64 && f <= CB_FRSZ2_32; }
 inline int frsz2_bits_of(int f) {
     return f == CB_FRSZ2_16 || f == CB_FRSZ2_16_B64 ? 16 : f == CB_FRSZ2_21 ? 21
@@ -168,20 +168,21 @@ struct Epi;  // last-workgroup reduction / solver step logic (epilogue.hpp)
 void launch_store(int fmt, const cb_basis& V, int col, const double* w, const double* divisor,
                   double* v_out, int32_t* flag, const int* guard, hipStream_t s);
 void launch_load(int fmt, const cb_basis& V, int col, double* x, hipStream_t s);
-// h = V^T w: partials[c * G + g] for c < j, then the epilogue e (its counter
-// must read 0) forms and uses the sums.
 // h = V^T w in one launch, for short vectors (false: not launched)
 bool launch_project_column(int fmt, const cb_basis& V, int j, const double* w, double* h, hipStream_t s);
+// h = V^T w: partials[c * G + g] for c < j, G of them a column (returned), then the
+// epilogue e forms and uses the sums (its counters must read 0; none with
+// EPI_PARTIALS: launch_reduce's work).
 int launch_project(int fmt, const cb_basis& V, int j, const double* w, double* partials,
                     const int* guard, const Epi& e, hipStream_t s);
 // w += sign * V h (h device); with partials != NULL also ||w||^2 per
-// workgroup and the epilogue e on it.
+// workgroup, as many as returned, and the epilogue e on it.
 int launch_subtract(int fmt, const cb_basis& V, int j, const int* jdev, const double* h,
                      double* w, double* partials, const int* guard, int accumulate_sign,
                      const Epi& e, hipStream_t s);
 // w -= V h (h device, j coefficients), then partials of u = V^T w (c < j) and
-// ||w||^2 (c = j), and the epilogue e (FUSED_CHECK).
-// (capacity: doubles of `partials`)
+// ||w||^2 (c = j), as many a column as returned, and the epilogue e (FUSED_CHECK,
+// or EPI_PARTIALS).  capacity: doubles of `partials`.
 int launch_subtract_project(int fmt, const cb_basis& V, int j, const double* h, double* w, double* partials,
                             int64_t capacity, const int* guard, const Epi& e, hipStream_t s);
 // Stage 2: out[c] (op 0: =, op 1: +=) = sum_g partials[c * G + g], c < ncols.

@@ -514,8 +514,9 @@ static int solve_impl(const cb_csr& A, const double* b, double* x, int m, double
             // when the last cycle re-orthogonalised at least half its steps
             // (the first cycle assumes so); the decision depends on the
             // solve's own history only.  A float64 basis keeps the separate
-            // launches: with 16-byte-per-lane float64 tiles the fused kernel
-            // holds half as many loads in flight and measured no faster.
+            // launches, as the option documents: the fused kernel that read each
+            // column twice measured no faster.  (The present one does: 255 -> 156
+            // us at 10^6 x 100; fuse_updates = 2 asks for it.)
             if (cycles > 0) {
                 const int steps_done = hs->iters - prev_iters;
                 fused = steps_done > 0 && 2 * (hs->reorths - prev_reorths) >= steps_done;

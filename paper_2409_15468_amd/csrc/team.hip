@@ -113,10 +113,12 @@ TeamSeats::~TeamSeats() {
 bool team_shape(int32_t n, int32_t m, int capacity, TeamShape* s) {
     if (m > kTeamMaxRestart || capacity < 1) return false;
     const int64_t tiles = (padded_rows(n) + kTile - 1) / kTile;
-    // At least two waves to a tile (half a million rows on 256 CUs).  With one,
-    // a wave walks all columns of its tile as the launch-per-kernel path's do,
-    // and a step gains nothing (n = 10^6, frsz2_32: 66 to 69 ms a solve
-    // either way), while the team keeps other streams off the CUs.
+    // At least two waves to a tile (half a million rows on 256 CUs).  With one, a
+    // wave walks all columns of its tile as the launch-per-kernel path's do: at n =
+    // 10^6 a solve alone took 68.9 -> 65.9 ms (frsz2_32), 48.9 -> 44.9 (frsz2_16)
+    // and 105 -> 95 (float64), but it holds every CU for that long, and what a team
+    // gains alone it loses beside others (four host threads' solves of 493,000
+    // rows, frsz2_32: 13.0 ms each by teams, 9.0 by launches).
     for (int cs = 8; cs >= 2; cs /= 2) {
         const int64_t G = (tiles + 8 / cs - 1) / (8 / cs);
         if (G <= capacity) {
