@@ -1,6 +1,6 @@
 // Per-wavefront tile operations on basis columns shared by the multi-workgroup
-// kernels and the resident solvers (teams, one workgroup per system): encode a tile of 512 rows into
-// a column, the fused decode + projection over a range of columns, and the
+// kernels and the resident solvers (teams, one workgroup per system): encode a
+// tile of 512 rows into a column, the fused decode + projection over a range of columns, and the
 // fused decode + multi-axpy.  Whole wavefronts call them (block maxima and
 // reductions use cross-lane moves).
 #pragma once
