@@ -52,7 +52,7 @@ int team_stream_groups(hipStream_t s) {
     const int cap = team_device_groups();
     int dev = 0, cus = 0;
     uint32_t mask[32] = {};
-    if (!s || s == hipStreamPerThread || cap == 0 || hipGetDevice(&dev) != hipSuccess ||
+    if (!s || s == hipStreamLegacy || s == hipStreamPerThread || cap == 0 || hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         return cap;
     if (hipExtStreamGetCUMask(s, 32, mask) != hipSuccess) {

@@ -169,3 +169,36 @@ def test_update_of_more_row_groups_than_workgroups(fmt):
     assert np.all(np.abs(wd.cpu().numpy() - ref) <= 1e-14 * (np.abs(w) + np.abs(dec) @ np.abs(h)))
     nr = oracle.dot(ref, ref)
     assert abs(norm2.item() - nr) <= 1e-13 * nr
+
+
+@pytest.mark.parametrize("fmt", ["frsz2_21", "float64"])
+def test_gram_schmidt_step_in_a_graph(fmt):
+    """Projection, fused update + projection and update with norm captured on
+    their first calls and replayed between eager work: each replay gives the eager
+    step's bits."""
+    n, j = 300007, 20
+    V, _, _ = build_basis(fmt, n, j, seed=5)
+    w0 = torch.from_numpy(np.random.default_rng(6).standard_normal(n)).cuda()
+    w = w0.clone()
+    h, u = (torch.empty(j + k, dtype=torch.float64, device="cuda") for k in (0, 1))
+    norm2 = torch.empty(1, dtype=torch.float64, device="cuda")
+    work = torch.empty((cb.cb_reduce_workspace_bytes(n, j + 1) + 7) // 8, dtype=torch.float64, device="cuda")
+
+    def step():
+        cb.cb_cgs_project(V, j, w, h=h, work=work)
+        cb.cb_cgs_subtract_project(V, j, h, w, out=u, work=work)
+        cb.cb_cgs_subtract(V, j, u, w, norm2=norm2, work=work)
+
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        step()
+    for _ in range(3):
+        w.copy_(w0)
+        g.replay()
+        torch.cuda.synchronize()
+        got = [t.clone() for t in (h, u, w, norm2)]
+        w.copy_(w0)
+        step()
+        torch.cuda.synchronize()
+        for a, b in zip(got, (h, u, w, norm2)):
+            assert torch.equal(a, b)

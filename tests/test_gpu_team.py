@@ -23,9 +23,9 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 
-def near_diagonal(n, seed, wide_row=None, width=600):
+def near_diagonal(n, seed, wide_row=None):
     """Rows of 4 on the diagonal with up to four neighbours at distances 1 and
-    37; row wide_row (if given) has `width` entries of 1/width."""
+    37; row wide_row (if given) has 600 entries of 1/600."""
     rng = np.random.default_rng(seed)
     i = np.arange(n)
     offs = np.array([-37, -1, 0, 1, 37])
@@ -37,8 +37,8 @@ def near_diagonal(n, seed, wide_row=None, width=600):
     c, v = cols[keep], vals[keep]
     if wide_row is not None:
         off = rows != wide_row
-        wide = np.unique(np.append(rng.choice(n, width, replace=False), wide_row))
-        wv = np.full(wide.size, 1.0 / width)
+        wide = np.unique(np.append(rng.choice(n, 600, replace=False), wide_row))
+        wv = np.full(wide.size, 1.0 / 600)
         wv[wide == wide_row] = 4.0
         at = np.searchsorted(rows, wide_row)
         rows = np.concatenate([rows[:at], np.full(wide.size, wide_row), rows[at:][off[at:]]])
