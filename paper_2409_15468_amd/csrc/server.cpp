@@ -63,7 +63,7 @@ struct Request {
 struct cb_server {
     size_t budget;
     int device;
-    int32_t team_wait;  // of the thread that created the server (cb_internal_team_wait)
+    int32_t team_wait, team_poll;  // of the thread that created the server (cb_internal_team_wait, _poll)
     std::chrono::steady_clock::time_point t0;
     std::mutex mu;
     std::condition_variable cv;
@@ -208,6 +208,7 @@ static bool has_kind(const cb_server* S, bool batch_lane) {
 static void worker_main(cb_server* S) {
     (void)hipSetDevice(S->device);
     cb_internal_team_wait(S->team_wait, 0);
+    cb_internal_team_poll(S->team_poll);
     hipStream_t s = nullptr;
     if (hipStreamCreateWithFlags(&s, hipStreamNonBlocking) != hipSuccess) return;
     const bool batch_lane = false;
@@ -341,6 +342,7 @@ static void solve_left(std::vector<InFlight>& left, unsigned char* dev, hipStrea
 static void ring_main(cb_server* S) {
     (void)hipSetDevice(S->device);
     cb_internal_team_wait(S->team_wait, 0);
+    cb_internal_team_poll(S->team_poll);
     hipStream_t ks = nullptr, us = nullptr;  // the loop's launches, and what they leave unsolved
     BatchRing* ring = nullptr;
     unsigned char* dev = nullptr;
@@ -544,6 +546,7 @@ cb_server* cb_server_create(size_t hbm_budget_bytes, int device, int lanes) {
     S->budget = hbm_budget_bytes;
     S->device = device;
     S->team_wait = team_wait_setting();
+    S->team_poll = team_poll_us();
     S->t0 = std::chrono::steady_clock::now();
     for (int i = 0; i < lanes; ++i) S->workers.emplace_back(worker_main, S);
     S->workers.emplace_back(ring_main, S);

@@ -134,7 +134,8 @@ int64_t team_ll_words(int G, int m) {
     return kJoinWords + (G <= kDirect ? (int64_t)4 * G * (m + 2) : (int64_t)2 * (G + 1) * (m + 2));
 }
 
-static thread_local int32_t g_wait_us = -1, g_wait_skip = 0, g_missed = 0;
+static thread_local int32_t g_wait_us = -1, g_wait_skip = 0, g_missed = 0, g_poll_us = -1;
+int32_t team_poll_us() { return g_poll_us < 0 ? kTeamPollUs : g_poll_us; }
 int32_t team_wait_setting() { return g_wait_us; }
 int32_t team_wait_us() {
     if (g_wait_us >= 0 && g_wait_skip-- <= 0) return g_wait_us;
@@ -186,3 +187,8 @@ extern "C" void cb_internal_team_wait(int32_t us, int32_t launches) {
     cb::g_wait_us = us;
     cb::g_wait_skip = launches;
 }
+
+// The limit of an exchange in the launches of this host thread, in microseconds
+// (negative: the default).  With 0 a team whose workgroups wait for one that is
+// slower by some hundred polls is lost, and the tests reach what follows.
+extern "C" void cb_internal_team_poll(int32_t us) { cb::g_poll_us = us; }

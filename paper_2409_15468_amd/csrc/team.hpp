@@ -11,7 +11,7 @@ constexpr int kTeamMaxGroups = 256;   // one workgroup per CU
 // State::status of a solve whose workgroups did not come together: nothing but
 // this word has been written
 constexpr int kTeamAbandoned = -1;
-// ... and of one in which a workgroup that had come was not heard of for 20 s
+// ... and of one in which a workgroup that had come was not heard of for kTeamPollUs
 // (its queue was taken off the GPU): x holds each row before or after the last
 // cycle's update, the counters are those of the cycles before
 constexpr int kTeamLost = -2;
@@ -24,6 +24,7 @@ constexpr int kTeamLost = -2;
 // solves they are, and one that forms restores it.
 constexpr int32_t kTeamWaitUs = 500000;
 constexpr int32_t kTeamWaitLeastUs = 2000;
+constexpr int32_t kTeamPollUs = 20000000;
 constexpr int kJoinWords = 16;  // ahead of the exchange slots, in a line of its own
 
 struct State;
@@ -55,6 +56,7 @@ struct TeamArgs {
     int32_t format;      // basis format (launches of many systems)
     int32_t wait_us;     // the team's workgroups come within this time or not at all (0: not at all)
     uint32_t epoch0;     // tags of this solve are above it; the slots hold none that are
+    int32_t poll_us;     // a whole team's exchange takes this long at most
 };
 
 struct TeamShape {
@@ -79,6 +81,8 @@ inline void team_exchange(TeamArgs& a, uint64_t* p) {
 int32_t team_wait_us();
 void team_waited(bool formed);
 int32_t team_wait_setting();
+// kTeamPollUs, or what cb_internal_team_poll has set for this host thread.
+int32_t team_poll_us();
 // Clear the words at a.join and start the team on stream s.
 void launch_team(int fmt, const TeamArgs& a, hipStream_t s);
 // The team for one of many systems; depends on its rows only.
@@ -115,3 +119,4 @@ private:
 }  // namespace cb
 
 extern "C" void cb_internal_team_wait(int32_t us, int32_t launches);
+extern "C" void cb_internal_team_poll(int32_t us);

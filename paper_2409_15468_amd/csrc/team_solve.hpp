@@ -61,7 +61,6 @@ constexpr int kTC = kTM + 2;            // columns of one exchange at most
 constexpr int kDirect = 32;             // workgroups up to which everyone reads all partials
 constexpr int kStage = 512;             // nonzeros of a 64-row block staged in LDS
 constexpr int64_t kStreamBytes = (int64_t)192 << 20;  // columns that the Infinity Cache does not keep
-constexpr uint64_t kPollTicks = 2000000000;  // 20 s of the 100 MHz counter
 constexpr unsigned kNoTeam = 1u << 31;      // in the join word
 
 struct TeamShared {
@@ -114,8 +113,8 @@ __device__ __forceinline__ void ll_store(uint64_t* s, double v, uint32_t tag) {
     __hip_atomic_store(s, t | lo32(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(s + 1, t | hi32(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// Waits for K slots at once (those with live[k]); after kPollTicks the team is
-// lost, and S.dead says so.
+// Waits for K slots at once (those with live[k]); after poll_us the team is lost,
+// and S.dead says so.
 template <int K>
 __device__ __forceinline__ bool ll_load(const Ctx& x, const uint64_t* const* s, const bool* live, uint32_t tag, double* v) {
     uint64_t t_end = 0;
@@ -135,7 +134,7 @@ __device__ __forceinline__ bool ll_load(const Ctx& x, const uint64_t* const* s, 
         if (ok) return true;
         if ((it & 255u) == 255u) {
             const uint64_t now = __builtin_amdgcn_s_memrealtime();
-            if (t_end == 0) t_end = now + kPollTicks;
+            if (t_end == 0) t_end = now + (uint64_t)x.S.args.poll_us * 100u;
             else if (now > t_end) {
                 x.S.dead = 1;
                 return false;
@@ -147,9 +146,9 @@ __device__ __forceinline__ bool ll_load(const Ctx& x, const uint64_t* const* s, 
 // True once all G workgroups of the team are on the GPU; false, in every one of
 // them, if they are not within wait_us (all threads).  Where a launch's
 // workgroups go on to other systems, the time counts while none of its teams is
-// whole: then every workgroup of it that the GPU has is in this one.    The count and the
-// decision against the team share a word: a workgroup gives up by setting the top
-// bit of a count that is not full, and a count with that bit is never full.
+// whole: then every workgroup of it that the GPU has is in this one.  The count
+// and the decision against the team share a word: a workgroup gives up by setting
+// the top bit of a count that is not full, and a count with that bit is never full.
 __device__ __forceinline__ bool gather(Ctx& x) {
     if (threadIdx.x == 0) {
         unsigned* join = x.arg(&TeamArgs::join);

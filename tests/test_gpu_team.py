@@ -338,6 +338,55 @@ def test_a_thousand_small_requests_in_flight():
     assert {(r[1]["status"], r[1]["iterations"]) for r in got.values()} == {(cb.CB_ERR_NOT_CONVERGED, 20000)}
 
 
+def test_a_team_that_is_lost():
+    """A row of some 10^5 entries keeps one workgroup at its product for
+    milliseconds.  With a limit of 0 on the exchanges the others give up waiting
+    (every kernel ends by itself): the solve, the batch and a served request go
+    to their other paths with x as it was, and give those paths' bits."""
+    rng = np.random.default_rng(3)
+    for kind, n in (("solve", 100000), ("batch", 60000), ("served", 16000)):
+        A = near_diagonal(n, n)
+        M = A.scipy().tolil()
+        c = rng.choice(n, n - n // 8, replace=False) if kind != "served" else np.arange(n)
+        M[n // 3, c] = rng.uniform(-1, 1, c.size) / c.size
+        M[n // 3, n // 3] = 4.0
+        M = M.tocsr()
+        M.sort_indices()
+        A = synth.CSR(n, M.indptr.astype(np.int32), M.indices.astype(np.int32), M.data)
+        b, x0 = M @ rng.uniform(-1, 1, n), rng.uniform(-1, 1, n)
+        Ad, bd = cb.DeviceCSR.from_host(A.row_ptr, A.col, A.val), torch.from_numpy(b).cuda()
+        got = []
+        for wait, poll in ((-1, 0), (0, -1)):
+            print(f"{kind} wait {wait} poll {poll}", flush=True)
+            cb.lib().cb_internal_team_wait(wait, 0)
+            cb.lib().cb_internal_team_poll(poll)
+            try:
+                if kind == "served":
+                    srv = cb.Server(4 << 30, 0, lanes=1)
+                    t = srv.submit(A.row_ptr, A.col, A.val, b, 20, 1e-10, "frsz2_32", x0=x0)
+                    t0, r = time.time(), None
+                    while r is None and time.time() - t0 < 20:
+                        time.sleep(0.001)
+                        r = srv.poll(t, n)
+                    srv.close()
+                    x, res = r[0], r[1]
+                else:
+                    xd = torch.from_numpy(x0.copy()).cuda()
+                    if kind == "solve":
+                        res, _ = cb.cbgmres_solve(Ad, bd, xd, 20, 1e-10, "frsz2_32")
+                    else:
+                        res = cb.cbgmres_solve_batch([(Ad, bd, xd, 20, 1e-10, "frsz2_32")])[0]
+                    x = xd.cpu().numpy()
+            finally:
+                cb.lib().cb_internal_team_wait(-1, 0)
+                cb.lib().cb_internal_team_poll(-1)
+            assert res["status"] == 0 and res["converged"]
+            assert np.linalg.norm(b - M @ x) <= 1e-10 * (1 + 1e-6) * np.linalg.norm(b)
+            got.append((x, res["iterations"], res["restarts"]))
+        if kind != "served":  # (16000 entries may not take long enough to lose a team)
+            assert np.array_equal(got[0][0], got[1][0]) and got[0][1:] == got[1][1:]
+
+
 def test_served_small_then_large():
     """A small request starts the serving launch (128 workgroups); the larger
     ones after it need 138 and 256 of the GPU's CUs, so they run only if
