@@ -481,7 +481,7 @@ int solve_by_teams(const cb_batch_item* items, int count, const BatchOpts& o, cb
         a.max_iters = o.max_iters;
         a.literal = o.literal;
         a.wait_us = team_wait_us();
-        a.poll_us = team_poll_us();
+        a.poll_ticks = team_poll_ticks();
         ll_words += team_ll_words(a.G, a.m);
     }
     if (order.empty()) return CB_OK;

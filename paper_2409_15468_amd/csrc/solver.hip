@@ -378,7 +378,7 @@ static int solve_team(const cb_csr& A, const double* b, double* x, int m, int fm
     seats.wait();
     for (;;) {
         a.wait_us = team_wait_us();
-        a.poll_us = team_poll_us();
+        a.poll_ticks = team_poll_ticks();
         launch_team(fmt, a, s);
         CB_HIP(hipGetLastError());
         CB_HIP(hipMemcpyAsync(hs, a.st, sizeof(State), hipMemcpyDeviceToHost, s));

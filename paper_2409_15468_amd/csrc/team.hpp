@@ -48,6 +48,7 @@ struct TeamArgs {
     double* hist;        // NULL, or |g_{j+1}| per step of this launch
     double tol, eta;
     int64_t col_total;   // bytes of a column with its exponents
+    uint64_t poll_ticks; // a whole team's exchange takes this long at most (100 MHz)
     int32_t n, m, G, cs;
     int32_t max_iters, max_cycles, literal;
     int32_t hist_cap;    // entries of hist; the launch ends when a cycle may not fit
@@ -56,7 +57,6 @@ struct TeamArgs {
     int32_t format;      // basis format (launches of many systems)
     int32_t wait_us;     // the team's workgroups come within this time or not at all (0: not at all)
     uint32_t epoch0;     // tags of this solve are above it; the slots hold none that are
-    int32_t poll_us;     // a whole team's exchange takes this long at most
 };
 
 struct TeamShape {
@@ -83,6 +83,7 @@ void team_waited(bool formed);
 int32_t team_wait_setting();
 // kTeamPollUs, or what cb_internal_team_poll has set for this host thread.
 int32_t team_poll_us();
+inline uint64_t team_poll_ticks() { return (uint64_t)team_poll_us() * 100u; }
 // Clear the words at a.join and start the team on stream s.
 void launch_team(int fmt, const TeamArgs& a, hipStream_t s);
 // The team for one of many systems; depends on its rows only.

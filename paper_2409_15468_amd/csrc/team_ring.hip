@@ -287,7 +287,7 @@ int ring_publish(BatchRing* r, const cb_batch_item& q, const int32_t* h_row_ptr,
     team_exchange(d.a, ll);
     d.a.st = r->results_dev + slot;
     d.a.wait_us = team_wait_us();
-    d.a.poll_us = team_poll_us();
+    d.a.poll_ticks = team_poll_ticks();
     d.a.busy = r->busy;
     d.a.epoch0 = r->epoch[slot];
     d.h_row_ptr = h_row_ptr;

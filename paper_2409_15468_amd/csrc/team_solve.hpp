@@ -113,7 +113,7 @@ __device__ __forceinline__ void ll_store(uint64_t* s, double v, uint32_t tag) {
     __hip_atomic_store(s, t | lo32(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(s + 1, t | hi32(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// Waits for K slots at once (those with live[k]); after poll_us the team is lost,
+// Waits for K slots at once (those with live[k]); after poll_ticks the team is lost,
 // and S.dead says so.
 template <int K>
 __device__ __forceinline__ bool ll_load(const Ctx& x, const uint64_t* const* s, const bool* live, uint32_t tag, double* v) {
@@ -134,7 +134,7 @@ __device__ __forceinline__ bool ll_load(const Ctx& x, const uint64_t* const* s, 
         if (ok) return true;
         if ((it & 255u) == 255u) {
             const uint64_t now = __builtin_amdgcn_s_memrealtime();
-            if (t_end == 0) t_end = now + (uint64_t)x.S.args.poll_us * 100u;
+            if (t_end == 0) t_end = now + x.S.args.poll_ticks;
             else if (now > t_end) {
                 x.S.dead = 1;
                 return false;
