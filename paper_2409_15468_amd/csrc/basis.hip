@@ -176,12 +176,17 @@ __device__ __forceinline__ int load_coefficients(const int* __restrict__ guard, 
 // of workgroup g; partials[g] = sum of w[k]^2 over those rows after the update
 // (row groups in order, then the waves in order), if partials != NULL, and
 // then the epilogue.
+// frsz2_21 leaves the lanes' addresses to the compiler: with scalar bases its
+// loop took 51.6 us instead of 48.6 at 10^6 x 90 and 33.8 instead of 32.2 at
+// 1000003 x 60 (909 and 912 at 2^24 x 101), and a solve at 10^6 x 100 58.4 ms
+// instead of 57.8; its projection takes the same time either way.
 template <int FMT, int U>
 __global__ __launch_bounds__(kThreads) void k_subtract(BasisView V, int j, const int* __restrict__ jdev,
                                                        const double* __restrict__ h,
                                                        double* __restrict__ w,
                                                        double* __restrict__ partials, int sign, int stream,
                                                        const int* __restrict__ guard, Epi e) {
+    constexpr int A = FMT == CB_FRSZ2_21 ? kLane : 0;
     __shared__ double elds[kEpiLds];
     // the coefficients (written by an earlier kernel), read once into LDS
     __shared__ double hc[kMaxRestart + 1];
@@ -199,11 +204,11 @@ __global__ __launch_bounds__(kThreads) void k_subtract(BasisView V, int j, const
         for (int q = 0; q < 8; ++q) acc[q] = 0.0;
         const bool full = tile0 + kTile <= V.np;
         if (stream) {
-            if (full) subtract_tile<FMT, U, kFull | kStream>(V, j, hc, tile0, lane, acc);
-            else subtract_tile<FMT, U, kStream>(V, j, hc, tile0, lane, acc);
+            if (full) subtract_tile<FMT, U, kFull | kStream | A>(V, j, hc, tile0, lane, acc);
+            else subtract_tile<FMT, U, kStream | A>(V, j, hc, tile0, lane, acc);
         } else {
-            if (full) subtract_tile<FMT, U, kFull>(V, j, hc, tile0, lane, acc);
-            else subtract_tile<FMT, U, 0>(V, j, hc, tile0, lane, acc);
+            if (full) subtract_tile<FMT, U, kFull | A>(V, j, hc, tile0, lane, acc);
+            else subtract_tile<FMT, U, A>(V, j, hc, tile0, lane, acc);
         }
         double wv[8];
         load_rows<FMT>(w, tile0, lane, V.n, wv);

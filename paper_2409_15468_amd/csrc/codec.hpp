@@ -46,8 +46,9 @@ __device__ __forceinline__ uint4 ld16(const void* p) {
 }
 // Load mode of a tile: bit 0 the tile lies wholly inside the column (no row
 // checks), bit 1 non-temporal loads, bit 2 buffer loads bounded by the column's
-// rows (a tile partly or wholly past them reads as 0 there, without conditions).
-constexpr int kFull = 1, kStream = 2, kBound = 4;
+// rows (a tile partly or wholly past them reads as 0 there, without conditions),
+// bit 3 the lane's addresses left to the compiler (frsz2_21 only, and not with bit 2).
+constexpr int kFull = 1, kStream = 2, kBound = 4, kLane = 8;
 __device__ __forceinline__ uint32_t word_of(const uint4& a, int i) {
     return i == 0 ? a.x : i == 1 ? a.y : i == 2 ? a.z : a.w;
 }
@@ -450,12 +451,18 @@ struct Tile<CB_FRSZ2_21> {
     int live;
     template <int LM>
     __device__ __forceinline__ void load(const BasisView& V, int col, int tile0, int lane) {
-        const unsigned char* base = scalar_base(V.column(col) + (int64_t)(tile0 >> 5) * 84);
+        const unsigned char* base = V.column(col) + (int64_t)(tile0 >> 5) * 84;
+        const uint32_t* ex = V.column_exps(col) + (tile0 >> 5);
+        uint32_t lo = (uint32_t)lane * 16u, le = (uint32_t)lane >> 2 << 2;
+        if constexpr ((LM & kLane) == 0) {
+            base = scalar_base(base);
+            ex = scalar_base(ex);
+            lo = lane_offset(lo);
+            le = lane_offset(le);
+        }
         // bytes of whole blocks below np (a piece that straddles their end
         // stays inside the column's 256-byte-rounded storage)
         const int vbytes = (LM & kFull) ? 1344 : (tile_rows(V.np, tile0) >> 5) * 84;
-        const uint32_t lo = lane_offset((uint32_t)lane * 16u);
-        const uint32_t* ex = scalar_base(V.column_exps(col) + (tile0 >> 5));
         if constexpr ((LM & kBound) != 0) {
             const Run run(base, (vbytes + 15) & ~15);
             a = run.b16(lo);
@@ -463,7 +470,7 @@ struct Tile<CB_FRSZ2_21> {
             // (rows past the end that share a piece with the last block decode
             // to less than 2^-1040: exponent 0)
             live = 1;
-            e = Run(ex, vbytes / 84 * 4).b4(lane_offset((uint32_t)lane >> 2 << 2));
+            e = Run(ex, vbytes / 84 * 4).b4(le);
             return;
         }
         a = 16 * lane < vbytes ? ld16<(LM & kStream) != 0>(at(base, lo)) : make_uint4(0, 0, 0, 0);
@@ -471,7 +478,7 @@ struct Tile<CB_FRSZ2_21> {
                                                       : make_uint4(0, 0, 0, 0);
         const int r = tile0 + 8 * lane;
         live = (LM & kFull) || r < V.np;
-        e = live ? *at(ex, lane_offset((uint32_t)lane >> 2 << 2)) : 0u;
+        e = live ? *at(ex, le) : 0u;
     }
     __device__ __forceinline__ void codes(uint32_t* c) const {
         const int lane = threadIdx.x & 63;
