@@ -640,9 +640,11 @@ constexpr int kFewColumns = 12;
 constexpr int64_t kFewBytes = 56000000;
 
 // What the exchange between a tile's waves costs a round of the one-read kernel,
-// in columns: frsz2_32 at 500009 x 8 takes 12.6 us with W = 1 and 14.0 with 2, one
-// round each, and at 300007 x 17 17.1 and 13.7.
-constexpr int kExchangeColumns = 4;
+// in columns.  Over 91 random sizes timed with each W (eight formats, 6*10^4 to
+// 2*10^6 rows, 3 to 52 columns) the choice with one is 1.3% above the fastest, with
+// four 2.2%: that stays with few waves too long (frsz2b64_32 at 597306 x 22 24.8 us
+// with W = 2, 22.1 with 8; float32 at 1230550 x 16 26.1 with 1, 21.1 with 4).
+constexpr int kExchangeColumns = 1;
 
 // Workgroups of that kernel with W waves a tile: what the GPU holds, cut to the
 // partial sums there is room for (capacity doubles) and to the fewest that take
